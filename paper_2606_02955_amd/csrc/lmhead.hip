@@ -8,24 +8,19 @@
 // the per-position outputs and the selection are then those of
 // fdllm_confidence / fdllm_decode_step (Sec. 3 "Notation"; Alg. 1).
 //
-// Three plans, by the number of positions N = B L:
-//   N <= 32     k_lm_stream: W streamed once, hidden operands in registers,
-//               logits folded in the kernel (HBM-bound);
-//   N <= 64     k_lm_kstream + k_lm_ksum: the same with the hidden dimension
-//               split over two workgroups, partial logits in the workspace;
-//   otherwise   k_lm_partial: MFMA tiles of 256 positions x 256 rows
-//               (bound by the matrix cores at large N);
-// each followed by k_lm_finish, which combines the per-split states.
+// Two plans, by the number of positions N = B L:
+//   N <= 32     k_lm_stream (d a multiple of 512 up to 4096): W streamed once,
+//               hidden operands in registers, logits folded in the kernel;
+//   otherwise   MFMA tiles of 256 vocabulary rows x 32 to 256 positions, the
+//               width chosen on the device by the number of candidates:
+//               k_lm_narrow (at most 128, HBM-bound), k_lm_wide (HBM-bound
+//               up to about 200, then bound by the matrix cores);
+// each followed by k_lm_finish, which combines the per-workgroup states.
 //
-// Main loop of the partial kernel: a workgroup of 8 waves owns 256 candidate
-// positions x 256 vocabulary rows per tile; the hidden dimension streams in
-// stages of 64 elements (128 bytes of every weight and hidden row, so each
-// load uses whole cache lines; 32 KiB of weights and 32 KiB of hidden states
-// per stage) that buffer_load ... lds writes straight into LDS, three weight
-// and two hidden stages resident (160 KiB).  One barrier per stage; each
-// wave's 64 MFMAs of a stage are interleaved with the reads of the next half
-// stage's operands, and the second half with the loads of the hidden part of
-// the stage after next and the weight part of the one after that.
+// Main loop of the tiles: a workgroup of 8 waves; the hidden dimension streams
+// in stages of 64 elements (128 bytes of every weight and hidden row, so each
+// load uses whole cache lines) that buffer_load ... lds writes straight into
+// LDS, two to four stages resident (up to 160 KiB), one barrier per stage.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -46,15 +41,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLmWaves = 8;                    // waves per workgroup
-constexpr int kLmVt = 256;                     // vocabulary rows per tile (MFMA A operand)
-constexpr int kLmPt = 256;                     // positions per workgroup (MFMA B operand)
-constexpr int kLmBK = 64;                      // hidden-dimension elements per LDS stage
 constexpr int kLmThreads = kLmWaves * kWave;
-constexpr int kLmRows = kLmPt;                 // candidate rows per workgroup
-constexpr int kLmCols = kLmVt;                 // vocabulary columns per tile
 
 // Candidate rows of every sequence, compacted (any order: a row's result
-// does not depend on the rows it shares a tile with); default outputs for
+// does not depend on where it sits in a tile); default outputs for
 // every other position.  One wavefront per sequence.
 __global__ void __launch_bounds__(256)
 k_lm_compact(const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
@@ -79,6 +69,63 @@ k_lm_compact(const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstar
   }
 }
 
+// The same for at most kLmOneWg positions, in position order, by one
+// workgroup: a launch less (no counter to clear first) and one round trip to
+// memory, every load issued at once.
+constexpr int kLmOneThreads = 1024;
+constexpr int kLmOneChunks = 8;
+constexpr int kLmOneWg = kLmOneThreads * kLmOneChunks;
+
+__global__ void __launch_bounds__(kLmOneThreads)
+k_lm_compact_one(const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
+                 const int32_t* __restrict__ bend, int B, int L, int32_t* __restrict__ rows,
+                 int32_t* __restrict__ count, RowOut out) {
+  constexpr int kWaves = kLmOneThreads / kWave;
+  __shared__ int s_n[kLmOneChunks * kWaves];      // candidates of chunk c, wave w
+  const int n = B * L;
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  int s[kLmOneChunks], e[kLmOneChunks], q[kLmOneChunks];
+  bool m[kLmOneChunks];
+#pragma unroll
+  for (int c = 0; c < kLmOneChunks; ++c) {
+    const int i = c * kLmOneThreads + (int)threadIdx.x;
+    const int ic = i < n ? i : 0;                 // past the end: position 0, not used
+    const int b = ic / L;
+    q[c] = ic - b * L;
+    s[c] = bstart[b];
+    e[c] = bend[b];
+    m[c] = mask[ic] != 0;
+  }
+  unsigned long long bal[kLmOneChunks];
+#pragma unroll
+  for (int c = 0; c < kLmOneChunks; ++c) {
+    const int i = c * kLmOneThreads + (int)threadIdx.x;
+    const bool cand = i < n && m[c] && window_ok(s[c], e[c], L) && q[c] >= s[c] && q[c] < e[c];
+    if (i < n && !cand) store_default(out, (size_t)i);
+    bal[c] = __ballot(cand);
+    if (lane == 0) s_n[c * kWaves + wave] = __popcll(bal[c]);
+  }
+  __syncthreads();
+  // lane l of every wave: the entries 2 l and 2 l + 1 and an inclusive scan
+  static_assert(kLmOneChunks * kWaves == 2 * kWave, "two entries a lane");
+  const int n0 = s_n[2 * lane], n1 = s_n[2 * lane + 1];
+  int incl = n0 + n1;
+#pragma unroll
+  for (int x = 1; x < kWave; x <<= 1) {
+    const int o = __shfl_up(incl, x);
+    if (lane >= x) incl += o;
+  }
+  const int excl = incl - n0 - n1;
+#pragma unroll
+  for (int c = 0; c < kLmOneChunks; ++c) {
+    const int k = c * kWaves + wave;              // wave-uniform
+    const int base = __shfl(excl, k / 2) + (k % 2 ? __shfl(n0, k / 2) : 0);
+    if ((bal[c] >> lane) & 1ull)
+      rows[base + __popcll(bal[c] & ((1ull << lane) - 1ull))] = c * kLmOneThreads + (int)threadIdx.x;
+  }
+  if (threadIdx.x == kWave - 1) *count = incl;
+}
+
 __global__ void k_lm_zero(int32_t* __restrict__ p) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
@@ -91,33 +138,40 @@ struct LmState {
   int first;
 };
 
-// Folds the lane's accumulators of one position (vocabulary entries
-// base + 16 mi + i, increasing in (mi, i)) into its state.
+// the exponent reference of a running maximum (kRefFloor before any element)
+__device__ __forceinline__ float lm_ref(float M) { return fmaxf(exp_ref(M), kRefFloor); }
+
+// Folds the lane's accumulators of one position, acc[.][0] (vocabulary
+// entries base + 16 mi + i, increasing in (mi, i)), into its state.
 template <int MI, int NI>
-__device__ __forceinline__ void lm_fold(LmState& st, const f32x4 (&acc)[MI][NI], int ni, int base,
-                                        int V) {
+__device__ __forceinline__ void lm_fold_first(LmState& st, f32x4 (&acc)[MI][NI], int base, int v_end,
+                                              bool partial) {
+  if (partial) {
+    // entries past the end take part in nothing: their terms are 0
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[mi][0][i] = 16 * mi + i < v_end - base ? acc[mi][0][i] : kNegInf;
+  }
   float tm = kNegInf;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = base + 16 * mi + i;
-      if (v < V) tm = fmaxf(tm, acc[mi][ni][i]);
-    }
+    for (int i = 0; i < 4; ++i) tm = fmaxf(tm, acc[mi][0][i]);
+  float K = lm_ref(st.M);      // not kept in a register over the matrix loop
   if (tm > st.M) {
     const float Kn = exp_ref(tm);
-    st.S = rescale(st.S, st.K, Kn);
-    st.K = Kn;
+    st.S = rescale(st.S, K, Kn);
+    K = Kn;
     st.M = tm;
-    int f = 0x7fffffff;
+    int f = 0;
 #pragma unroll
     for (int mi = MI - 1; mi >= 0; --mi)
 #pragma unroll
-      for (int i = 3; i >= 0; --i) {
-        const int v = base + 16 * mi + i;
-        if (v < V && acc[mi][ni][i] == tm) f = v;
-      }
-    st.first = f;
+      for (int i = 3; i >= 0; --i)
+        if (acc[mi][0][i] == tm) f = 16 * mi + i;
+    st.first = base + f;
   }
   // every term enters a double sum on its own, so the greedy element's term
   // stays exact and s' = (S - e_M) / e_M keeps its relative accuracy
@@ -125,11 +179,31 @@ __device__ __forceinline__ void lm_fold(LmState& st, const f32x4 (&acc)[MI][NI],
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = base + 16 * mi + i;
-      sum[i & 1] += v < V ? (double)term(acc[mi][ni][i], st.K) : 0.0;
-    }
+    for (int i = 0; i < 4; ++i) sum[i & 1] += (double)term(acc[mi][0][i], K);
   st.S += sum[0] + sum[1];
+}
+
+// Folds all NI positions of a lane.  One body, run NI times with the
+// accumulators and states turned by one position each time: a tile's fold is
+// run once or twice in a launch, so its instructions come from memory, and
+// the time they take to arrive, not the arithmetic, is what it costs
+// (unrolled over the positions it added 12 us to a launch of 155 us that
+// reads 1 GB of weights for 32 positions).
+template <int MI, int NI>
+__device__ __forceinline__ void lm_fold(LmState (&st)[NI], f32x4 (&acc)[MI][NI], int base, int v_end,
+                                        bool partial) {
+#pragma unroll 1
+  for (int k = 0; k < NI; ++k) {
+    lm_fold_first<MI, NI>(st[0], acc, base, v_end, partial);
+    const LmState s0 = st[0];
+#pragma unroll
+    for (int ni = 0; ni + 1 < NI; ++ni) st[ni] = st[ni + 1];
+    st[NI - 1] = s0;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni + 1 < NI; ++ni) acc[mi][ni] = acc[mi][ni + 1];
+  }
 }
 
 __device__ __forceinline__ void lm_combine(LmState& st, float M2, float K2, double S2, int f2) {
@@ -141,29 +215,81 @@ __device__ __forceinline__ void lm_combine(LmState& st, float M2, float K2, doub
   st.first = min(fa, fb);
 }
 
+// ---- work division ----------------------------------------------------------
+// The number of candidates is on the device, so the division of the work is
+// too: kLmGroups workgroups (one per compute unit) read it and share the
+// (position tile, vocabulary range) plane evenly, whatever the span.  The
+// candidates are cut into the fewest tiles of at most 256 positions, and the
+// tiles are as narrow (32, 64, 128, 192, 256 positions) as then still holds
+// them: a narrow tile saves the matrix work and the reads of the hidden
+// states of positions that are not there.  With one position tile the
+// vocabulary is divided in steps of 16 rows, so every workgroup reads the
+// same number of weight rows; with several, in whole weight tiles, the
+// position tiles one after the other, so that the workgroups on the same
+// weight rows sit on the same XCD (their distance is a multiple of eight for
+// 2^k position tiles).
+constexpr int kLmGroups = 256;
+constexpr int kLmVt = 256;                     // vocabulary rows per tile (MFMA A operand)
+constexpr int kLmMaxPt = 256;                  // positions per tile at most (MFMA B operand)
+
+struct LmWork {
+  int mt, pt;        // position tiles and their width
+  int unit, nb;      // vocabulary rows per unit, units of the vocabulary
+  int groups;        // workgroups that have work
+};
+
+__host__ __device__ inline LmWork lm_work(int n, int V) {
+  LmWork w;
+  w.mt = (n + kLmMaxPt - 1) / kLmMaxPt;
+  const int per = w.mt ? (n + w.mt - 1) / w.mt : 0;
+  w.pt = per <= 32 ? 32 : per <= 64 ? 64 : per <= 128 ? 128 : per <= 192 ? 192 : 256;
+  w.unit = w.mt > 1 ? kLmVt : 16;
+  w.nb = (V + w.unit - 1) / w.unit;
+  const long long t = (long long)w.mt * w.nb;
+  w.groups = t < kLmGroups ? (int)t : kLmGroups;
+  return w;
+}
+// first unit of workgroup g (units of all position tiles, one tile after the
+// other), floor(g T / groups) for T units; workgroup g takes
+// [lm_first(g), lm_first(g + 1)).  No division: fewer units than workgroups
+// are one each, else groups is a power of two.
+static_assert((kLmGroups & (kLmGroups - 1)) == 0, "shifts in lm_first");
+__host__ __device__ inline long long lm_first(const LmWork& w, int g) {
+  if (w.groups < kLmGroups) return g;
+  const long long t = (long long)w.mt * w.nb;
+  return g * (t / kLmGroups) + g * (t % kLmGroups) / kLmGroups;
+}
+// the workgroup that holds unit u: the largest g with lm_first(g) <= u
+__host__ __device__ inline int lm_owner(const LmWork& w, long long u) {
+  if (w.groups < kLmGroups) return (int)u;
+  if (w.mt == 1) return u == 0 ? 0 : u == w.nb - 1 ? kLmGroups - 1 : (int)(((u + 1) * kLmGroups - 1) / w.nb);
+  return (int)(((u + 1) * kLmGroups - 1) / ((long long)w.mt * w.nb));
+}
+// partials per position: the workgroups that a position tile can meet
+__host__ __device__ inline int lm_stride(const LmWork& w) {
+  return w.mt <= 1 ? w.groups : w.groups / w.mt + 2;
+}
+// most partials that any number of candidates up to n needs
+static size_t lm_max_partials(long long n) {
+  const long long one = (n < kLmMaxPt ? n : kLmMaxPt) * (long long)kLmGroups;
+  const long long mt = (n + kLmMaxPt - 1) / kLmMaxPt;
+  return (size_t)(one + (mt > 1 ? mt * kLmMaxPt * 2 : 0));
+}
+
 // ---- LDS-DMA main loop -----------------------------------------------------
-// Stages of kLmBK hidden elements: 256 weight rows and 256 hidden rows of
+// Stages of kLmBK hidden elements: VT weight rows and PT hidden rows of
 // kLmBK * 2 bytes each, written by buffer_load ... lds (each lane of a wave
-// instruction fills the next 16 bytes of LDS).  The weight part runs one
-// stage further ahead (three buffers; it comes from HBM or the Infinity
-// Cache) than the hidden part (two buffers; mostly L2 hits); both are loaded
-// into the buffers of the stage just read, in the second half of the current
-// stage.  Rows are stored unpadded; the 16-byte vector s of row r
+// instruction fills the next 16 bytes of LDS), WB weight and HB hidden stages
+// resident.  Rows are stored unpadded; the 16-byte vector s of row r
 // sits in slot s ^ lm_swz(r).  lm_swz was chosen from LDS bank-conflict
 // counter measurements of ds_read_b128 patterns on gfx950: with it the
 // operand reads (lane l: row l % 16, vector 4 h + l / 16) are conflict-free.
+constexpr int kLmBK = 64;                                 // hidden elements per stage
 constexpr int kLmSlots = kLmBK / 8;                       // 16-byte vectors per row and stage
 constexpr int kLmRowBytes = kLmBK * 2;
-constexpr int kLmWBytes = kLmVt * kLmRowBytes;            // weight part of a stage
 constexpr int kLmDmaRows = kWave / kLmSlots;              // rows per wave-wide load
+constexpr int kLmWBytes = kLmVt * kLmRowBytes;            // weight part of a stage
 constexpr int kLmWDma = kLmVt / kLmDmaRows / kLmWaves;    // weight loads per wave and stage
-constexpr int kLmHDma = kLmPt / kLmDmaRows / kLmWaves;
-constexpr int kLmDmaPerStage = kLmWDma + kLmHDma;
-constexpr int kLmWBuf = 3, kLmHBuf = 2;                  // weight and hidden stages resident
-constexpr int kLmHBytes = kLmPt * kLmRowBytes;            // hidden part of a stage
-constexpr int kLmHOff = kLmWBuf * kLmWBytes;              // hidden buffers after the weight ones
-constexpr size_t kLmLdsBytes = (size_t)kLmWBuf * kLmWBytes + (size_t)kLmHBuf * kLmHBytes;
-static_assert(kLmWDma == 4 && kLmHDma == 4, "the interleaved schedule issues four loads of each");
 
 __device__ __forceinline__ int lm_swz(int r) { return (r & 1) | ((r >> 1) & 2) | ((r << 1) & 4); }
 
@@ -186,11 +312,18 @@ __device__ __forceinline__ i32x4 lm_rsrc(const void* base, uint32_t bytes) {
 // byte lds + 16 i.  Issued as inline assembly: the compiler cannot tell which
 // buffer such a load writes and would drain every load in flight before the
 // next LDS read; the explicit vmcnt waits of lm_sync are the ones needed.
+// NT: data that no other workgroup reads (nontemporal).
+template <bool NT>
 __device__ __forceinline__ void lm_dma(i32x4 rsrc, uint32_t lds, uint32_t voff, int soff) {
   int keep;   // m0 is the compiler's register: saved and restored around the load
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\t"
-               "s_mov_b32 m0, %0"
-               : "=&s"(keep) : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen nt lds\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(keep) : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  else
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(keep) : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 // waits until at most N of this wave's loads are outstanding and its LDS
@@ -203,90 +336,130 @@ __device__ __forceinline__ void lm_sync() {
 
 #define LM_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// the producer: the next stage this wave loads (tile relative to the
-// workgroup's first, stage within the tile), the buffer it goes to, and the
-// lane's load offsets.  Past the last stage the last one is loaded again
-// (into a buffer nobody reads any more), so every stage issues the same
-// number of loads.
-struct LmProducer {
-  int tile, ks, left, buf;        // weight stages
-  int hks, hleft, hbuf;           // hidden stages (one behind)
-  i32x4 wr, hr;
-  uint32_t w_voff[kLmWDma], h_voff[kLmHDma];
-  uint32_t lds_w[kLmWDma], lds_h[kLmHDma];   // wave's LDS offsets within a stage
+// Shape of a tile's main loop: WV x WP waves over VT x PT, each MI x NI MFMA
+// blocks of 16 x 16; WB weight and HB hidden stages resident.
+template <int PT_, int WV_, int WB_, int HB_>
+struct LmShape {
+  static constexpr int PT = PT_, WV = WV_, WP = kLmWaves / WV_, WB = WB_, HB = HB_;
+  static constexpr int MI = kLmVt / WV / 16, NI = PT / WP / 16;
+  static constexpr int HDma = PT >= 64 ? PT / kLmDmaRows / kLmWaves : 1;   // hidden loads per wave and stage
+  static constexpr int HBytes = PT * kLmRowBytes;
+  static constexpr int HOff = WB * kLmWBytes;               // hidden buffers after the weight ones
+  static constexpr int Bytes = WB * kLmWBytes + HB * HBytes;
 };
+constexpr size_t kLmLdsBytes = 160 * 1024;
+constexpr int kLmStageBytes = 144 * 1024;                   // the narrow tiles' stages
 
-__device__ __forceinline__ void lm_tile_setup(LmProducer& p, const uint16_t* weight, int t, int V,
-                                              int d, int lane, int wave) {
-  const int n0 = t * kLmVt;
-  const uint32_t row_bytes = (uint32_t)d * 2u;
-  p.wr = lm_rsrc(weight + (size_t)n0 * d, kLmVt * row_bytes);
-  const int lr = lane / kLmSlots, ls = lane % kLmSlots;
-#pragma unroll
-  for (int j = 0; j < kLmWDma; ++j) {
-    const int r = (wave * kLmWDma + j) * kLmDmaRows + lr;
-    const int v = min(n0 + r, V - 1) - n0;              // rows past the vocabulary repeat the last
-    p.w_voff[j] = (uint32_t)v * row_bytes + (uint32_t)((ls ^ lm_swz(r)) * 16);
-  }
+// Rows a multiple of 4 KiB apart have their elements k in the same few memory
+// channels, and all workgroups read the same k at the same time.  So half of
+// them go through the hidden dimension with each two neighbouring blocks of
+// 16 stages (2 KiB of a row) exchanged: 64 positions at d = 4096,
+// V = 126464 190 -> 162 us.  The even and the odd blocks are summed apart and
+// added at the end, so a logit's bits do not depend on which workgroup formed
+// it (equal weight rows tie, whatever their places).
+constexpr int kLmFlip = 16;
+__device__ __forceinline__ int lm_flip(int g, int nks) {
+  return nks % (2 * kLmFlip) == 0 && (g / 8) % 2 ? kLmFlip : 0;
 }
 
-// grid (position tiles, vocabulary splits).  A workgroup takes kLmPt
-// candidate positions and the split's vocabulary tiles of kLmVt rows; wave w
-// computes vocabulary rows 128 (w % 2) .. +127 of a tile against positions
-// 64 (w / 2) .. +63 as 8 x 4 MFMA 16x16x32 blocks, vocabulary along the MFMA
-// rows: lane l holds positions 16 ni + l % 16 and, for each, vocabulary rows
-// 16 mi + 4 (l / 16) + i of the wave's 128.
-__global__ void __launch_bounds__(kLmThreads)
-k_lm_partial(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
-             const int32_t* __restrict__ rows, const int32_t* __restrict__ count, int d, int V,
-             int tiles_per_split, uint32_t hid_bytes, WavePartial* __restrict__ partials, int n_split) {
+// the producer: the next stage this wave loads (tile relative to the
+// segment's first, stage within the tile), the buffer it goes to, and the
+// lane's load offsets.  Stage i of a tile holds the hidden elements
+// [64 k, 64 k + 64) with k = i ^ flip (lm_flip).  Past the last stage the last one is
+// loaded again (into a buffer nobody reads any more), so every stage issues
+// the same number of loads.
+template <class Sh>
+struct LmProducer {
+  int tile, ks, left, buf;        // weight stages
+  int hks, hleft, hbuf;           // hidden stages
+  i32x4 wr, hr;
+  uint32_t w_voff[kLmWDma], h_voff[Sh::HDma];
+  uint32_t lds_w, lds_h;          // the wave's LDS offsets within a stage
+};
+
+// weight rows [n0, min(n0 + 256, v_end)); the rows past v_end are out of the
+// resource's range: no memory is read for them (they are masked in the fold)
+template <class Sh>
+__device__ __forceinline__ void lm_tile_setup(LmProducer<Sh>& p, const uint16_t* weight, int n0,
+                                              int v_end, int d) {
+  p.wr = lm_rsrc(weight + (size_t)n0 * d, (uint32_t)min(kLmVt, v_end - n0) * (uint32_t)d * 2u);
+}
+
+struct LmArgs {
+  const uint16_t* hidden;
+  const uint16_t* weight;
+  int32_t* rows;           // candidates, in any order, and their number (workspace)
+  int32_t* count;
+  WavePartial* partials;
+  int d, V;
+  uint32_t hid_bytes;
+};
+
+// One segment: `cnt` candidates from rank p0 (at most PT) against the
+// vocabulary rows [v_beg, v_end); partials at [p0 + i] * stride + split.
+// Wave w computes vocabulary rows 16 MI (w % WV) .. of a tile against
+// positions 16 NI (w / WV) .. as MI x NI MFMA 16x16x32 blocks, vocabulary
+// along the MFMA rows: lane l holds positions 16 ni + l % 16 and, for each,
+// vocabulary rows 16 mi + 4 (l / 16) + i of the wave's.
+template <class Sh, bool NT>
+__device__ __forceinline__ void lm_segment(const LmArgs& a, const int32_t* rows, int p0, int cnt, int v_beg,
+                                           int v_end, int flip, int stride, int split) {
+  constexpr int MI = Sh::MI, NI = Sh::NI, WV = Sh::WV;
+  constexpr int NL = kLmWDma + Sh::HDma;
+  // the interleaved schedule: one wave tile of 128 x (48 or 64)
+  constexpr bool kInterleaved = MI == 8;
+  static_assert(Sh::Bytes <= (int)(Sh::PT <= 128 ? kLmStageBytes : kLmLdsBytes), "stages fit the LDS");
   extern __shared__ __attribute__((aligned(1024))) char lm_lds[];
   const int tid = threadIdx.x;
   const int lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int vw = wave % 2, pw = wave / 2;
-  const int nrows = *count;
-  const int p0 = blockIdx.x * kLmPt;
-  if (p0 >= nrows) return;
-  const int n_tiles = (V + kLmVt - 1) / kLmVt;
-  const int t_begin = blockIdx.y * tiles_per_split;
-  const int t_end = min(t_begin + tiles_per_split, n_tiles);
-  const int nks = d / kLmBK;
+  const int vw = wave % WV, pw = wave / WV;
+  const int d = a.d, nks = d / kLmBK;
+  const int n_tiles = (v_end - v_beg + kLmVt - 1) / kLmVt;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lm_lds;
 
-  LmProducer pr;
+  LmProducer<Sh> pr;
   pr.tile = 0;
   pr.ks = 0;
-  pr.left = (t_end - t_begin) * nks;
+  pr.left = n_tiles * nks;
   pr.buf = 0;
   pr.hks = 0;
   pr.hleft = pr.left;
   pr.hbuf = 0;
-  pr.hr = lm_rsrc(hidden, hid_bytes);
+  pr.hr = lm_rsrc(a.hidden, a.hid_bytes);
+  auto hidden_rows = [&]() {
+    const int lr = lane / kLmSlots, ls = lane % kLmSlots;
+#pragma unroll
+    for (int j = 0; j < Sh::HDma; ++j) {
+      const int first = ((wave * Sh::HDma + j) * kLmDmaRows) % Sh::PT;
+      const int r = first + lr;
+      // positions past the end repeat the others, spread over them
+      const int q = p0 + (r < cnt ? r : r % cnt);
+      pr.h_voff[j] = (uint32_t)rows[q] * (uint32_t)d * 2u + (uint32_t)((ls ^ lm_swz(r)) * 16);
+      if (j == 0) pr.lds_h = lds0 + (uint32_t)(Sh::HOff + first * kLmRowBytes);
+    }
+  };
   {
     const int lr = lane / kLmSlots, ls = lane % kLmSlots;
 #pragma unroll
-    for (int j = 0; j < kLmHDma; ++j) {
-      const int r = (wave * kLmHDma + j) * kLmDmaRows + lr;
-      const int q = p0 + r < nrows ? p0 + r : p0;       // past the end: repeat the first row
-      pr.h_voff[j] = (uint32_t)rows[q] * (uint32_t)d * 2u + (uint32_t)((ls ^ lm_swz(r)) * 16);
-      pr.lds_h[j] = (uint32_t)(kLmHOff + (wave * kLmHDma + j) * kLmDmaRows * kLmRowBytes);
+    for (int j = 0; j < kLmWDma; ++j) {
+      const int r = (wave * kLmWDma + j) * kLmDmaRows + lr;
+      pr.w_voff[j] = (uint32_t)r * (uint32_t)d * 2u + (uint32_t)((ls ^ lm_swz(r)) * 16);
     }
-#pragma unroll
-    for (int j = 0; j < kLmWDma; ++j)
-      pr.lds_w[j] = (uint32_t)((wave * kLmWDma + j) * kLmDmaRows * kLmRowBytes);
+    pr.lds_w = lds0 + (uint32_t)(wave * kLmWDma * kLmDmaRows * kLmRowBytes);
   }
-  lm_tile_setup(pr, weight, t_begin, V, d, lane, wave);
+  lm_tile_setup(pr, a.weight, v_beg, v_end, d);
 
-  // the loads of the producers' stages: H j (j < 4) of the hidden producer,
-  // then W j - 4 of the weight producer (one stage ahead)
+  // the loads of the producers' stages: H j (j < HDma) of the hidden
+  // producer, then W j - HDma of the weight producer
   auto dma = [&](int j) {
-    if (j < kLmHDma)
-      lm_dma(pr.hr, lds0 + (uint32_t)pr.hbuf * kLmHBytes + pr.lds_h[j], pr.h_voff[j],
-             pr.hks * kLmRowBytes);
+    if (j < Sh::HDma)
+      lm_dma<false>(pr.hr, pr.lds_h + (uint32_t)(pr.hbuf * Sh::HBytes + j * kWave * 16), pr.h_voff[j],
+                    __builtin_amdgcn_readfirstlane((pr.hks ^ flip) * kLmRowBytes));
     else
-      lm_dma(pr.wr, lds0 + (uint32_t)pr.buf * kLmWBytes + pr.lds_w[j - kLmHDma],
-             pr.w_voff[j - kLmHDma], pr.ks * kLmRowBytes);
+      lm_dma<NT>(pr.wr, pr.lds_w + (uint32_t)(pr.buf * kLmWBytes + (j - Sh::HDma) * kWave * 16),
+                 pr.w_voff[j - Sh::HDma],
+                 __builtin_amdgcn_readfirstlane((pr.ks ^ flip) * kLmRowBytes));
   };
   auto advance_w = [&]() {
     if (pr.left > 1) {
@@ -294,146 +467,384 @@ k_lm_partial(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ w
       if (++pr.ks == nks) {
         pr.ks = 0;
         ++pr.tile;
-        lm_tile_setup(pr, weight, t_begin + pr.tile, V, d, lane, wave);
+        lm_tile_setup(pr, a.weight, v_beg + pr.tile * kLmVt, v_end, d);
       }
     }
-    pr.buf = pr.buf + 1 == kLmWBuf ? 0 : pr.buf + 1;
+    pr.buf = pr.buf + 1 == Sh::WB ? 0 : pr.buf + 1;
   };
   auto advance_h = [&]() {
     if (pr.hleft > 1) {
       --pr.hleft;
       if (++pr.hks == nks) pr.hks = 0;
     }
-    pr.hbuf ^= 1;
+    pr.hbuf = pr.hbuf + 1 == Sh::HB ? 0 : pr.hbuf + 1;
   };
 
   // operand addresses of this lane: row l % 16 of a 16-row block, 16-byte
   // vector 4 h + l / 16 of the stage's 64 hidden elements in half h
-  uint32_t a_addr[2], b_addr[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const uint32_t slot = (uint32_t)(((4 * h + lane / 16) ^ lm_swz(lane % 16)) * 16);
-    a_addr[h] = (uint32_t)((128 * vw + lane % 16) * kLmRowBytes) + slot;
-    b_addr[h] = (uint32_t)(kLmHOff + (64 * pw + lane % 16) * kLmRowBytes) + slot;
-  }
-  auto lds_at = [&](uint32_t a) -> bf16x8 {
-    return *reinterpret_cast<const bf16x8*>(lm_lds + (a - lds0));
+  const uint32_t slot0 = (uint32_t)((lane / 16 ^ lm_swz(lane % 16)) * 16);
+  const uint32_t a_addr0 = (uint32_t)((16 * MI * vw + lane % 16) * kLmRowBytes) + slot0;
+  const uint32_t b_addr0 = (uint32_t)(Sh::HOff + (16 * NI * pw + lane % 16) * kLmRowBytes) + slot0;
+  constexpr uint32_t kHalf = 64;    // half 1: vector 4 + ..., bit 6 of the address (rows are 128 bytes)
+  auto lds_at = [&](uint32_t at) -> bf16x8 {
+    return *reinterpret_cast<const bf16x8*>(lm_lds + (at - lds0));
   };
 
-  LmState st[4];
+  LmState st[NI];
 #pragma unroll
-  for (int ni = 0; ni < 4; ++ni) st[ni] = LmState{kNegInf, kRefFloor, 0.0, 0x7fffffff};
+  for (int ni = 0; ni < NI; ++ni) st[ni] = LmState{kNegInf, kRefFloor, 0.0, 0x7fffffff};   // K unused here
 
-  f32x4 acc[8][4];
-  bf16x8 fa[8], fb[4], nb4[4], na7;
-#define LM_M(mi, ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0)
-  // the 32 MFMAs of one half stage on (fa, fb); the operands of the next half
-  // stage (weight operands at sa, hidden operands at sb) are read as the
-  // registers they replace fall dead; with_loads also issues the stage loads
-  auto half = [&](uint32_t sa, uint32_t sb, bool with_loads) {
-    LM_M(0, 0); LM_FENCE(); nb4[0] = lds_at(sb); LM_FENCE();
-    LM_M(0, 1); LM_FENCE(); nb4[1] = lds_at(sb + 16 * kLmRowBytes); LM_FENCE();
-    LM_M(0, 2); LM_FENCE(); nb4[2] = lds_at(sb + 32 * kLmRowBytes); LM_FENCE();
-    LM_M(0, 3); LM_FENCE(); nb4[3] = lds_at(sb + 48 * kLmRowBytes); LM_FENCE();
+  auto zero = [&](f32x4 (&acc)[MI][NI]) {
 #pragma unroll
-    for (int mi = 1; mi < 8; ++mi) {
-      LM_M(mi, 0); LM_FENCE();
-      fa[mi - 1] = lds_at(sa + (mi - 1) * 16 * kLmRowBytes); LM_FENCE();
-      LM_M(mi, 1); LM_FENCE();
-      if (with_loads) { dma(mi - 1); LM_FENCE(); }
-      if (mi == 7) { na7 = lds_at(sa + 7 * 16 * kLmRowBytes); LM_FENCE(); }
-      LM_M(mi, 2); LM_FENCE();
-      if (with_loads && mi == 7) { dma(7); LM_FENCE(); }
-      LM_M(mi, 3); LM_FENCE();
-    }
+    for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) fb[ni] = nb4[ni];
-    fa[7] = na7;
-  };
-
-  // prologue: stages 0 and 1 of both, and the weight part of stage 2, in
-  // flight (in this order), then wait for stage 0
-  for (int s = 0; s < 2; ++s) {
-#pragma unroll
-    for (int j = 0; j < kLmDmaPerStage; ++j) dma(j);
-    advance_h();
-    advance_w();
-  }
-#pragma unroll
-  for (int j = kLmHDma; j < kLmDmaPerStage; ++j) dma(j);
-  advance_w();
-  lm_sync<kLmDmaPerStage + kLmWDma>();
-#pragma unroll
-  for (int ni = 0; ni < 4; ++ni) fb[ni] = lds_at(lds0 + b_addr[0] + ni * 16 * kLmRowBytes);
-#pragma unroll
-  for (int mi = 0; mi < 8; ++mi) fa[mi] = lds_at(lds0 + a_addr[0] + mi * 16 * kLmRowBytes);
-
-  int wbuf = 0, hbuf = 0;     // buffers of the stage being consumed
-  for (int t = t_begin; t < t_end; ++t) {
-#pragma unroll
-    for (int mi = 0; mi < 8; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[mi][ni][i] = 0.0f;
-    for (int ks = 0; ks < nks; ++ks) {
-      const uint32_t cw = lds0 + (uint32_t)wbuf * kLmWBytes, ch = lds0 + (uint32_t)hbuf * kLmHBytes;
-      const int nwbuf = wbuf + 1 == kLmWBuf ? 0 : wbuf + 1, nhbuf = hbuf ^ 1;
-      const uint32_t nw = lds0 + (uint32_t)nwbuf * kLmWBytes, nh = lds0 + (uint32_t)nhbuf * kLmHBytes;
-      // first half: MFMAs on the stage's half 0, its half 1 read in between
-      LM_FENCE();
-      half(cw + a_addr[1], ch + b_addr[1], false);
-      // every wave has read all of this stage's buffers, and the next stage
-      // has landed (only the weight part of the one after is outstanding)
-      LM_FENCE();
-      lm_sync<kLmWDma>();
-      // second half: MFMAs on half 1; the next stage's half 0 read, and the
-      // hidden part of the stage after next and the weight part of the one
-      // after that loaded into this stage's buffers, in between
-      half(nw + a_addr[0], nh + b_addr[0], true);
-      LM_FENCE();
+  };
+  auto fold = [&](int t, f32x4 (&acc)[MI][NI]) {
+    const int n0 = v_beg + t * kLmVt;
+    lm_fold<MI, NI>(st, acc, n0 + 16 * MI * vw + 4 * (lane / 16), v_end, n0 + kLmVt > v_end);
+  };
+
+  if constexpr (kInterleaved) {
+    // three weight stages and two hidden ones: the weight part, from HBM or
+    // the Infinity Cache, runs one stage further ahead than the hidden part,
+    // mostly L2 hits.  Both are loaded into the buffers of the stage just
+    // read, in the second half of the current stage.
+    static_assert(Sh::WB == 3 && Sh::HB == 2 && kLmWDma == 4, "the schedule's waits");
+    f32x4 acc[MI][NI];
+    bf16x8 fa[8], fb[NI], nfb[NI], na7;
+#define LM_M(mi, ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0)
+    // the MFMAs of one half stage on (fa, fb); the operands of the next half
+    // stage (weight operands at sa, hidden operands at sb) are read as the
+    // registers they replace fall dead; with_loads also issues the stage loads
+    auto half = [&](uint32_t sa, uint32_t sb, bool with_loads) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) {
+        LM_M(0, ni); LM_FENCE();
+        nfb[ni] = lds_at(sb + (uint32_t)(16 * ni * kLmRowBytes)); LM_FENCE();
+      }
+#pragma unroll
+      for (int mi = 1; mi < 8; ++mi) {
+        LM_M(mi, 0); LM_FENCE();
+        fa[mi - 1] = lds_at(sa + (uint32_t)((mi - 1) * 16 * kLmRowBytes)); LM_FENCE();
+        LM_M(mi, 1); LM_FENCE();
+        if (with_loads && mi - 1 < NL) { dma(mi - 1); LM_FENCE(); }
+        if (mi == 7) { na7 = lds_at(sa + (uint32_t)(7 * 16 * kLmRowBytes)); LM_FENCE(); }
+#pragma unroll
+        for (int ni = 2; ni < NI; ++ni) {
+          LM_M(mi, ni); LM_FENCE();
+          if (ni == 2 && with_loads && mi == 7 && NL > 7) { dma(7); LM_FENCE(); }
+        }
+      }
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) fb[ni] = nfb[ni];
+      fa[7] = na7;
+    };
+
+    hidden_rows();
+    // prologue: stages 0 and 1 of both, and the weight part of stage 2, in
+    // flight (in this order), then wait for stage 0
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) dma(j);
       advance_h();
       advance_w();
-      wbuf = nwbuf;
-      hbuf = nhbuf;
     }
-    const int base = t * kLmVt + 128 * vw + 4 * (lane / 16);
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) lm_fold<8, 4>(st[ni], acc, ni, base, V);
-  }
+    for (int j = Sh::HDma; j < NL; ++j) dma(j);
+    advance_w();
+    lm_sync<NL + kLmWDma>();
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) fb[ni] = lds_at(lds0 + b_addr0 + ni * 16 * kLmRowBytes);
+#pragma unroll
+    for (int mi = 0; mi < 8; ++mi) fa[mi] = lds_at(lds0 + a_addr0 + mi * 16 * kLmRowBytes);
+
+    int wbuf = 0, hbuf = 0;     // buffers of the stage being consumed
+    for (int t = 0; t < n_tiles; ++t) {
+      zero(acc);
+      for (int ks = 0; ks < nks; ++ks) {
+        const uint32_t cw = lds0 + (uint32_t)wbuf * kLmWBytes, ch = lds0 + (uint32_t)hbuf * Sh::HBytes;
+        const int nwbuf = wbuf + 1 == Sh::WB ? 0 : wbuf + 1, nhbuf = hbuf ^ 1;
+        const uint32_t nw = lds0 + (uint32_t)nwbuf * kLmWBytes, nh = lds0 + (uint32_t)nhbuf * Sh::HBytes;
+        // first half: MFMAs on the stage's half 0, its half 1 read in between
+        LM_FENCE();
+        half((cw + a_addr0) ^ kHalf, (ch + b_addr0) ^ kHalf, false);
+        // every wave has read all of this stage's buffers, and the next stage
+        // has landed (only the weight part of the one after is outstanding)
+        LM_FENCE();
+        lm_sync<kLmWDma>();
+        // second half: MFMAs on half 1; the next stage's half 0 read, and the
+        // hidden part of the stage after next and the weight part of the one
+        // after that loaded into this stage's buffers, in between
+        half(nw + a_addr0, nh + b_addr0, true);
+        LM_FENCE();
+        advance_h();
+        advance_w();
+        wbuf = nwbuf;
+        hbuf = nhbuf;
+      }
+      fold(t, acc);
+    }
 #undef LM_M
-  // lanes l, l^16, l^32, l^48 hold the same positions
+  } else {
+    // narrow tiles, bound by the read of the weights: D stages resident, one
+    // barrier a stage; the loads of the stage D - 1 ahead go out first, into
+    // the buffers that every wave finished reading before the barrier.  The
+    // sums of the even and of the odd 16-stage blocks are kept apart (lm_flip)
+    // and, where the registers allow it, formed in chains of 8 stages: the
+    // error of a chain of float32 sums grows with its length.
+    constexpr int D = Sh::WB, NH = Sh::HDma, kChain = 8;
+    static_assert(Sh::HB == D && (D == 3 || D == 4), "equal stages");
+    // the weights of the first stages, before the positions are looked up
 #pragma unroll
-  for (int ni = 0; ni < 4; ++ni) {
+    for (int s = 0; s < D - 1; ++s) {
 #pragma unroll
-    for (int x = 16; x <= 32; x *= 2) {
-      const float M2 = __shfl_xor(st[ni].M, x);
-      const float K2 = __shfl_xor(st[ni].K, x);
-      const double S2 = __shfl_xor(st[ni].S, x);
-      const int f2 = __shfl_xor(st[ni].first, x);
-      lm_combine(st[ni], M2, K2, S2, f2);
+      for (int j = NH; j < NL; ++j) dma(j);
+      advance_w();
+    }
+    hidden_rows();
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s) {
+#pragma unroll
+      for (int j = 0; j < NH; ++j) dma(j);
+      advance_h();
+    }
+    int buf = 0, done = 0;
+    for (int t = 0; t < n_tiles; ++t) {
+      f32x4 cur[MI][NI], other[MI][NI];     // even and odd blocks, in turn
+      zero(cur);
+      zero(other);
+      auto add = [&](f32x4 (&to)[MI][NI], const f32x4 (&x)[MI][NI]) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) to[mi][ni] += x[mi][ni];
+      };
+      auto stages = [&](f32x4 (&acc)[MI][NI], int count) {
+        for (int k = 0; k < count; ++k) {
+          // stage `done` has landed: outstanding may be the hidden parts of
+          // the prologue's later stages and whole stages issued since
+          if (done == 0) lm_sync<(D - 2) * NH>();
+          else if (D == 4 && done == 1) lm_sync<NH + NL>();
+          else lm_sync<(D - 2) * NL>();
+          ++done;
+#pragma unroll
+          for (int j = 0; j < NL; ++j) dma(j);
+          advance_h();
+          advance_w();
+          const uint32_t cw = lds0 + (uint32_t)buf * kLmWBytes, ch = lds0 + (uint32_t)buf * Sh::HBytes;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            bf16x8 fa[MI], fb[NI];
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) fb[ni] = lds_at(((ch + b_addr0) ^ (h * kHalf)) + ni * 16 * kLmRowBytes);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) fa[mi] = lds_at(((cw + a_addr0) ^ (h * kHalf)) + mi * 16 * kLmRowBytes);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+              for (int ni = 0; ni < NI; ++ni)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0);
+          }
+          buf = buf + 1 == D ? 0 : buf + 1;
+        }
+      };
+      for (int k0 = 0; k0 < nks; k0 += kLmFlip) {
+        if constexpr (Sh::PT <= 64) {
+          for (int k1 = k0; k1 < min(nks, k0 + kLmFlip); k1 += kChain) {
+            f32x4 acc[MI][NI];
+            zero(acc);
+            stages(acc, min(kChain, nks - k1));
+            add(cur, acc);
+          }
+        } else {
+          stages(cur, min(kLmFlip, nks - k0));
+        }
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) {
+            const f32x4 x = cur[mi][ni];
+            cur[mi][ni] = other[mi][ni];
+            other[mi][ni] = x;
+          }
+      }
+      add(cur, other);
+      fold(t, cur);
     }
   }
-  // the two vocabulary halves of a position meet in LDS, once no load is
-  // still writing into it
+  // the 4 WV states of a position (lanes l, l + 16, l + 32, l + 48 of the WV
+  // waves on its vocabulary rows) meet in LDS, once no load is still writing
+  // into it; small loops for the same reason as in lm_fold
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  WavePartial* xch = reinterpret_cast<WavePartial*>(lm_lds);
   __syncthreads();
-  if (vw == 1 && lane < 16) {
+  constexpr int NS = 4 * WV, PP = kLmThreads / Sh::PT < NS ? kLmThreads / Sh::PT : NS;
+  constexpr int kPer = NS / PP;                 // states per thread in the first round
+  constexpr bool kAll = Sh::PT <= kLmThreads;
+  static_assert(kAll && NS % PP == 0 && NS * Sh::PT * 16 <= (int)kLmLdsBytes, "the exchange");
+  float* xm = reinterpret_cast<float*>(lm_lds);                       // [NS][PT] maxima
+  int* xf = reinterpret_cast<int*>(xm + NS * Sh::PT);                 // their indices
+  double* xs = reinterpret_cast<double*>(xf + NS * Sh::PT);           // sums
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
-      xch[64 * pw + 16 * ni + lane] = WavePartial{st[ni].M, st[ni].K, st[ni].S, st[ni].first};
+  for (int ni = 0; ni < NI; ++ni) {
+    const int at = (4 * vw + lane / 16) * Sh::PT + 16 * (NI * pw + ni) + lane % 16;
+    xm[at] = st[ni].M;
+    xf[at] = st[ni].first;
+    xs[at] = st[ni].S;
   }
   __syncthreads();
-  if (vw != 0 || lane >= 16) return;
-#pragma unroll
-  for (int ni = 0; ni < 4; ++ni) {
-    const WavePartial o = xch[64 * pw + 16 * ni + lane];
-    lm_combine(st[ni], o.m, o.K, o.S, o.first);
-    const int r = p0 + 64 * pw + 16 * ni + lane;
-    if (r < nrows)
-      partials[(size_t)r * n_split + blockIdx.y] = WavePartial{st[ni].M, st[ni].K, st[ni].S, st[ni].first};
+  const int r = tid % Sh::PT, part = tid / Sh::PT;
+  // adds `n` states of position r, from entry s0 on, `step` apart
+  auto meet = [&](int s0, int n, int step) {
+    LmState c{kNegInf, kRefFloor, 0.0, 0x7fffffff};
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+      const int at = (s0 + k * step) * Sh::PT + r;
+      const float m = xm[at];
+      lm_combine(c, m, lm_ref(m), xs[at], xf[at]);
+    }
+    return c;
+  };
+  if (part < PP) {
+    const LmState c = meet(part * kPer, kPer, 1);
+    const int at = part * kPer * Sh::PT + r;    // this thread's first entry
+    xm[at] = c.M;
+    xf[at] = c.first;
+    xs[at] = c.S;
   }
+  __syncthreads();
+  if (part == 0 && r < cnt) {
+    const LmState c = meet(0, PP, kPer);
+    a.partials[(size_t)(p0 + r) * stride + split] = WavePartial{c.M, c.K, c.S, c.first};
+  }
+  __syncthreads();   // the next segment loads into the buffers
+}
+
+// Workgroup g's segments.  Two kernels, each for its tile widths, both
+// launched where the candidates may be either (the other one's workgroups
+// leave at once): in one kernel the wide tiles' registers made the narrow
+// ones reload spilled values in the fold, and such a reload waits for every
+// weight load in flight.
+template <class F>
+__device__ __forceinline__ void lm_segments(const LmArgs& a, const LmWork& w, int n, F&& segment) {
+  const int g = blockIdx.x;
+  const int p_last = w.mt == 1 ? 0 : (int)((lm_first(w, g + 1) - 1) / w.nb);
+  for (int p = w.mt == 1 ? 0 : (int)(lm_first(w, g) / w.nb); p <= p_last; ++p) {
+    const long long u0 = (long long)p * w.nb;
+    const int b0 = (int)max(0ll, lm_first(w, g) - u0), b1 = (int)min((long long)w.nb, lm_first(w, g + 1) - u0);
+    // uniform values out of divisions: scalar registers
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int p0 = uni(p * w.pt), cnt = uni(min(w.pt, n - p0));
+    const int v_beg = uni(b0 * w.unit), v_end = uni(min(a.V, b1 * w.unit));
+    const int split = uni(g - lm_owner(w, u0)), stride = uni(lm_stride(w));
+    segment(p0, cnt, v_beg, v_end, stride, split);
+  }
+}
+
+// The candidate positions, in position order, found by every workgroup for
+// itself from at most kLmSelf positions (one round trip to memory instead of
+// a launch): the first kLmNarrow of them go to `list` (LDS), the number is
+// returned.  Workgroup 0 also writes them all out with their number, for the
+// kernels that follow, and the default outputs of the other positions.
+struct LmCand {
+  const uint8_t* mask;
+  const int32_t* bstart;
+  const int32_t* bend;
+  int B, L;
+  RowOut out;
+};
+constexpr int kLmNarrow = 128;                             // most candidates of the narrow kernel
+constexpr int kLmSelfChunks = 4;
+constexpr int kLmSelf = kLmSelfChunks * kLmThreads;        // 2048
+
+__device__ __forceinline__ int lm_find(const LmCand& c, int32_t* list, int* waves_n, int32_t* rows,
+                                       int32_t* count) {
+  const int n = c.B * c.L;
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  int s[kLmSelfChunks], e[kLmSelfChunks], q[kLmSelfChunks];
+  bool m[kLmSelfChunks];
+#pragma unroll
+  for (int k = 0; k < kLmSelfChunks; ++k) {
+    const int i = k * kLmThreads + (int)threadIdx.x;
+    const int ic = i < n ? i : 0;                          // past the end: position 0, not used
+    const int b = (int)((unsigned)ic / (unsigned)c.L);
+    q[k] = ic - b * c.L;
+    s[k] = c.bstart[b];
+    e[k] = c.bend[b];
+    m[k] = c.mask[ic] != 0;
+  }
+  unsigned long long bal[kLmSelfChunks];
+#pragma unroll
+  for (int k = 0; k < kLmSelfChunks; ++k) {
+    const int i = k * kLmThreads + (int)threadIdx.x;
+    const bool cand = i < n && m[k] && window_ok(s[k], e[k], c.L) && q[k] >= s[k] && q[k] < e[k];
+    if (blockIdx.x == 0 && i < n && !cand) store_default(c.out, (size_t)i);
+    bal[k] = __ballot(cand);
+    if (lane == 0) waves_n[k * kLmWaves + wave] = __popcll(bal[k]);
+  }
+  __syncthreads();
+  static_assert(kLmSelfChunks * kLmWaves <= kWave, "one lane per (chunk, wave)");
+  const int own = lane < kLmSelfChunks * kLmWaves ? waves_n[lane] : 0;
+  int incl = own;
+#pragma unroll
+  for (int x = 1; x < kLmSelfChunks * kLmWaves; x <<= 1) {
+    const int o = __shfl_up(incl, x);
+    if (lane >= x) incl += o;
+  }
+  const int total = __builtin_amdgcn_readlane(incl, kLmSelfChunks * kLmWaves - 1);
+#pragma unroll
+  for (int k = 0; k < kLmSelfChunks; ++k) {
+    const int base = __shfl(incl - own, k * kLmWaves + wave);
+    if ((bal[k] >> lane) & 1ull) {
+      const int at = base + __popcll(bal[k] & ((1ull << lane) - 1ull));
+      const int i = k * kLmThreads + (int)threadIdx.x;
+      if (at < kLmNarrow) list[at] = i;
+      if (blockIdx.x == 0) rows[at] = i;
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *count = total;
+  __syncthreads();
+  return total;
+}
+
+// at most kLmNarrow candidates.  Self: at most kLmSelf positions, compacted
+// here; otherwise the candidates were listed before.
+template <bool Self>
+__global__ void __launch_bounds__(kLmThreads) k_lm_narrow(LmArgs a, LmCand c) {
+  // the list sits behind the stages
+  extern __shared__ __attribute__((aligned(1024))) char lm_lds[];
+  int32_t* list = reinterpret_cast<int32_t*>(lm_lds + kLmStageBytes);
+  int n;
+  if constexpr (Self) n = lm_find(c, list, list + kLmNarrow, a.rows, a.count);
+  else n = *a.count;
+  n = __builtin_amdgcn_readfirstlane(n);
+  if (n == 0 || n > kLmNarrow) return;
+  const LmWork w = lm_work(n, a.V);
+  if ((int)blockIdx.x >= w.groups) return;
+  const int32_t* rows = Self ? list : a.rows;
+  const int flip = lm_flip((int)blockIdx.x, a.d / kLmBK);
+  lm_segments(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
+    if (w.pt == 32) lm_segment<LmShape<32, 8, 4, 4>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
+    else if (w.pt == 64) lm_segment<LmShape<64, 8, 3, 3>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
+    else lm_segment<LmShape<128, 4, 3, 3>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
+  });
+}
+
+// One: a single position tile (129..256 candidates), the weights read once;
+// otherwise more than 256 candidates.
+template <bool One>
+__global__ void __launch_bounds__(kLmThreads)
+k_lm_wide(LmArgs a) {
+  const int n = __builtin_amdgcn_readfirstlane(*a.count);
+  if (One ? (n <= 128 || n > kLmMaxPt) : n <= kLmMaxPt) return;
+  const LmWork w = lm_work(n, a.V);
+  if ((int)blockIdx.x >= w.groups) return;
+  lm_segments(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
+    if (w.pt == 192) lm_segment<LmShape<192, 2, 3, 2>, One>(a, a.rows, p0, cnt, v_beg, v_end, 0, stride, split);
+    else lm_segment<LmShape<256, 2, 3, 2>, One>(a, a.rows, p0, cnt, v_beg, v_end, 0, stride, split);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -650,292 +1061,68 @@ k_lm_stream(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ we
   }
 }
 
-// ---------------------------------------------------------------------------
-// 33..64 positions: the hidden dimension split over workgroups
-// ---------------------------------------------------------------------------
-// A CU's registers hold the hidden operands of about 32 positions at d = 4096,
-// so for up to 32 S positions the hidden dimension is cut into S parts of
-// d / S elements and workgroup g takes part g % S of the contiguous row range
-// of group g / S: W is still read once, in blocks of 8 S rows x d / S
-// elements (16 d bytes, 64 KiB at d = 4096; each row piece contiguous).  Wave
-// w owns the 16 positions of column block w % 2S and the (w / 2S)-th of the
-// part's elements (4 / S waves per column block), with those hidden operands
-// in registers (128 VGPRs at d = 4096).  The waves' products of a block meet
-// in LDS, where the next iteration adds the halves and writes the block's
-// logits over the part (float32, MFMA accumulation) as one contiguous run of
-// 16-byte vectors: plogits[part][v][position].  k_lm_ksum adds the S parts in
-// order and folds them.  The plan uses S = 2: with S = 4 (128 positions) the
-// partial logits' extra traffic (2 x 259 MB at V = 126464) and the 8-fold
-// LDS operand reads left it no faster than the tiled kernel.
-constexpr int kKsWaves = 8;
-
-// two sets of the waves' products: 8 waves x S / 2 row blocks x 1 KiB each
-template <int S>
-constexpr size_t ks_red_bytes() {
-  return 2 * (size_t)kKsWaves * (S / 2) * kWave * sizeof(f32x4);
-}
-// two row blocks and the products (144 KiB for S = 2 at d = 4096)
-template <int S>
-constexpr size_t ks_lds_bytes(int d) {
-  return 2 * (size_t)16 * d + ks_red_bytes<S>();
-}
-
-template <int DM, int S>
-__global__ void __launch_bounds__(kKsWaves * kWave)
-k_lm_kstream(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
-             const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
-             const int32_t* __restrict__ bend, int B, int L, int V, int32_t* __restrict__ rows,
-             int32_t* __restrict__ count, RowOut out, float* __restrict__ plogits) {
-  constexpr int d = DM * 512;
-  constexpr int dk = d / S;                                 // elements per part
-  constexpr int NP = kLsRows * S;                           // positions served
-  constexpr int NB = NP / 16;                               // 16-column MFMA blocks
-  constexpr int KW = kKsWaves / NB;                         // waves per column block
-  constexpr int dw = dk / KW;                               // elements per wave (d / 4)
-  constexpr int NC = dw / 32;                               // 32-element chunks per wave
-  constexpr int R = 8 * S;                                  // rows per block
-  constexpr int MB = R / 16;                                // 16-row MFMA blocks per block
-  constexpr int vec_part = dk / 8;                          // 16-byte vectors per row piece
-  constexpr int vec_row = d / 8;
-  constexpr uint32_t blk_bytes = (uint32_t)R * dk * 2;
-  constexpr int NL = (int)(blk_bytes / (kKsWaves * kWave * 16));  // loads per thread and block
-  static_assert(KW * NB == kKsWaves && MB >= 1 && NL == DM && NC >= 1, "k-split shape");
-  extern __shared__ __attribute__((aligned(1024))) char ks_lds[];
-  // products: float [set][wave][row block][element][lane]
-  float* red = reinterpret_cast<float*>(ks_lds + 2 * blk_bytes);
-  constexpr int red_set = kKsWaves * MB * 4 * kWave;              // floats per set
-  // the candidate list sits in the second set, first written after the
-  // loop's second barrier
-  int32_t* cand_rows = reinterpret_cast<int32_t*>(red + red_set);
-  int* cand_n = cand_rows + NP;
-  const int t = threadIdx.x;
-  const int lane = t % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
-  const int g = blockIdx.x;
-  const int kp = g % S;                                     // part of the hidden dimension
-  const int gr = g / S, GR = gridDim.x / S;                 // row-range group
-
-  // the candidate positions, in position order (B L <= NP)
-  if (wave == 0) {
-    const int n = B * L;
-    int base = 0;
-    for (int q0 = 0; q0 < NP; q0 += kWave) {
-      const int q = q0 + lane;
-      bool cand = false;
-      if (q < n) {
-        const int b = q / L, i = q % L;
-        const int s = bstart[b], e = bend[b];
-        cand = window_ok(s, e, L) && i >= s && i < e && mask[q] != 0;
-      }
-      const unsigned long long bal = __ballot(cand);
-      const int idx = base + __popcll(bal & ((1ull << lane) - 1ull));
-      if (cand) cand_rows[idx] = q;
-      if (g == 0) {
-        if (cand) rows[idx] = q;
-        else if (q < n) store_default(out, q);
-      }
-      base += __popcll(bal);
-    }
-    if (lane == 0) {
-      *cand_n = base;
-      if (g == 0) *count = base;
-    }
-  }
-  __syncthreads();
-  const int nrows = *cand_n;
-  if (nrows == 0) return;
-
-  const int nblk = (V + R - 1) / R;
-  const int b_beg = (int)((long long)gr * nblk / GR), b_end = (int)((long long)(gr + 1) * nblk / GR);
-  const int cnt = b_end - b_beg;
-  const int cb = wave % NB, kw = wave / NB;
-  const int k0 = kp * dk + kw * dw;                         // this wave's first element
-
-  // hidden operands of positions 16 cb + l % 16 (past the count: the first
-  // row; their logits are written but never folded)
-  u32x4 hb[NC];
-  {
-    const int q = 16 * cb + lane % 16;
-    const uint16_t* h = hidden + (size_t)cand_rows[q < nrows ? q : 0] * d + k0 + 8 * (lane / 16);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) hb[c] = *reinterpret_cast<const u32x4*>(h + 32 * c);
-  }
-  // block loads as in k_lm_stream, over the part's row pieces; LDS slot
-  // (row r, vector s) holds the piece's vector s ^ (r % 16), so the 16 rows
-  // an operand read touches sit in distinct banks
-  const u32x4* wv = reinterpret_cast<const u32x4*>(weight);
-  u32x4 stg[NL];
-  auto load_regs = [&](int i) {
-    const int vb = (b_beg + i) * R;
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int slot = j * kKsWaves * kWave + t;
-      const int v = min(vb + slot / vec_part, V - 1);       // rows past V repeat the last
-      stg[j] = __builtin_nontemporal_load(wv + (size_t)v * vec_row + kp * vec_part + slot % vec_part);
-    }
-  };
-  auto store_lds = [&](int buf) {
-    u32x4* bl = reinterpret_cast<u32x4*>(ks_lds + buf * blk_bytes);
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int slot = j * kKsWaves * kWave + t;
-      const int r = slot / vec_part, sv = slot % vec_part;
-      bl[r * vec_part + (sv ^ (r & 15))] = stg[j];
-    }
-  };
-  // logits of block i from the products in set i % 2: the block's R x NP
-  // floats are contiguous in plogits, one 16-byte vector (4 positions of a
-  // row) per thread and step; in the products, row r, position p of column
-  // block cb sits at element r % 4 of lanes 16 ((r % 16) / 4) + p % 16 of the
-  // waves kw NB + cb, row block r / 16
-  auto store_logits = [&](int i) {
-    constexpr int NV = R * NP / 4;                          // vectors per block
-    const float* rs = red + (i & 1) * red_set;
-    const int v0 = (b_beg + i) * R;
-#pragma unroll
-    for (int j = 0; j < (NV + kKsWaves * kWave - 1) / (kKsWaves * kWave); ++j) {
-      const int x = j * kKsWaves * kWave + t;
-      const int r = x / (NP / 4), p = 4 * (x % (NP / 4));
-      if (x < NV && v0 + r < V) {
-        const int cbx = p / 16;
-        const int off = ((r / 16) * 4 + r % 4) * kWave + 16 * ((r % 16) / 4) + p % 16;
-        f32x4 sum = *reinterpret_cast<const f32x4*>(rs + cbx * MB * 4 * kWave + off);
-#pragma unroll
-        for (int k = 1; k < KW; ++k)
-          sum += *reinterpret_cast<const f32x4*>(rs + (k * NB + cbx) * MB * 4 * kWave + off);
-        *reinterpret_cast<f32x4*>(plogits + ((size_t)kp * V + v0 + r) * NP + p) = sum;
-      }
-    }
-  };
-  const int ar = lane % 16;                                 // operand row within an MFMA block
-
-  load_regs(0);
-  store_lds(0);
-  __builtin_amdgcn_s_waitcnt(0x0f70);                       // vmcnt(0), as in k_lm_stream
-  if (cnt > 1) load_regs(1);
-  for (int it = 0; it < cnt; ++it) {
-    const int buf = it & 1;
-    // block it is in LDS; the products of block it - 1 are complete, and
-    // those of block it - 2 (this iteration's set) have been written out
-    __syncthreads();
-    if (it > 0) store_logits(it - 1);
-    const u32x4* bl = reinterpret_cast<const u32x4*>(ks_lds + buf * blk_bytes);
-    f32x4 acc[2][MB];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[h][mb][e] = 0.0f;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int sv = kw * (dw / 8) + 4 * c + lane / 16;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, bl[(16 * mb + ar) * vec_part + (sv ^ ar)]);
-        acc[c & 1][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, hb[c]),
-                                                                 acc[c & 1][mb], 0, 0, 0);
-      }
-    }
-    float* ws_ = red + (it & 1) * red_set + wave * MB * 4 * kWave + lane;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ws_[(mb * 4 + e) * kWave] = acc[0][mb][e] + acc[1][mb][e];
-    if (it + 1 < cnt) store_lds(buf ^ 1);
-    if (it + 2 < cnt) load_regs(it + 2);
-  }
-  __syncthreads();
-  store_logits(cnt - 1);
-}
-
-// Adds the S parts' logits of every candidate position, in part order, and
-// folds them: workgroup j takes the vocabulary entries [j chunk, (j+1) chunk);
-// thread t takes the 4 positions 4 (t % Q) .. +3 (Q = NP / 4) at every
-// (256 / Q)-th entry; the threads of a position are combined in order at the
-// end, one partial per (position, workgroup) for k_lm_finish.
-template <int S>
-__global__ void __launch_bounds__(256)
-k_lm_ksum(const float* __restrict__ plogits, const int32_t* __restrict__ count, int V, int chunk,
-          WavePartial* __restrict__ partials, int n_split) {
-  constexpr int NP = kLsRows * S, Q = NP / 4, VS = 256 / Q;
-  __shared__ WavePartial xs[VS][NP];
-  const int t = threadIdx.x, q = t % Q, vs = t / Q;
-  const int n = *count;
-  if (n == 0) return;
-  const int v0 = blockIdx.x * chunk, v1 = min(V, v0 + chunk);
-  LmState st[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) st[e] = LmState{kNegInf, kRefFloor, 0.0, 0x7fffffff};
-  for (int v = v0 + vs; v < v1; v += VS) {
-    f32x4 x = *reinterpret_cast<const f32x4*>(plogits + (size_t)v * NP + 4 * q);
-#pragma unroll
-    for (int k = 1; k < S; ++k) x += *reinterpret_cast<const f32x4*>(plogits + ((size_t)k * V + v) * NP + 4 * q);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (x[e] > st[e].M) {
-        const float Kn = exp_ref(x[e]);
-        st[e].S = rescale(st[e].S, st[e].K, Kn);
-        st[e].K = Kn;
-        st[e].M = x[e];
-        st[e].first = v;
-      }
-      st[e].S += (double)term(x[e], st[e].K);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) xs[vs][4 * q + e] = WavePartial{st[e].M, st[e].K, st[e].S, st[e].first};
-  __syncthreads();
-  if (t < n) {
-    LmState c = {xs[0][t].m, xs[0][t].K, xs[0][t].S, xs[0][t].first};
-#pragma unroll
-    for (int r = 1; r < VS; ++r) lm_combine(c, xs[r][t].m, xs[r][t].K, xs[r][t].S, xs[r][t].first);
-    partials[(size_t)t * n_split + blockIdx.x] = WavePartial{c.M, c.K, c.S, c.first};
-  }
-}
-
 // Per candidate row, one wavefront: lane l combines the splits l, l+64, ...
-// of the row's contiguous partials, then a fixed butterfly over the lanes
-// (both partners of every step form the same sum) and the finish.
-__global__ void __launch_bounds__(256)
-k_lm_finish(const int32_t* __restrict__ rows, const int32_t* __restrict__ count,
-            const WavePartial* __restrict__ partials, int n_split, RowOut out) {
+// of the row's contiguous partials, all loaded at once, then a fixed
+// butterfly over the lanes (both partners of every step form the same sum)
+// and the finish.
+constexpr int kLmFinishPer = (kLmGroups + 2 + kWave - 1) / kWave;   // partials per lane at most
+__device__ __forceinline__ void lm_finish_row(const WavePartial* p, int n_split, int row, RowOut out) {
   const int lane = threadIdx.x % kWave;
-  const int k = blockIdx.x * 4 + threadIdx.x / kWave;
-  if (k >= *count) return;
-  const WavePartial* p = partials + (size_t)k * n_split;
+  WavePartial q[kLmFinishPer];
+#pragma unroll
+  for (int i = 0; i < kLmFinishPer; ++i) {
+    const int j = lane + i * kWave;
+    q[i] = p[j < n_split ? j : 0];
+  }
   float M = kNegInf;
-  for (int j = lane; j < n_split; j += kWave) M = fmaxf(M, p[j].m);
+#pragma unroll
+  for (int i = 0; i < kLmFinishPer; ++i) M = fmaxf(M, q[i].m);
   M = wave_max(M);
   const float K = exp_ref(M);
   double S = 0.0;
   int first = 0x7fffffff;
-  for (int j = lane; j < n_split; j += kWave) {
-    const WavePartial q = p[j];
-    S += rescale(q.S, q.K, K);
-    if (q.m == M) first = min(first, q.first);
+#pragma unroll
+  for (int i = 0; i < kLmFinishPer; ++i) {
+    if (lane + i * kWave < n_split) S += rescale(q[i].S, q[i].K, K);
+    if (q[i].m == M) first = min(first, q[i].first);
   }
 #pragma unroll
   for (int d = kWave / 2; d >= 1; d >>= 1) S += __shfl_xor(S, d);
   first = wave_min(first);
-  if (lane == 0) store_row(out, (size_t)rows[k], finish_row(M, K, S, first));
+  if (lane == 0) store_row(out, (size_t)row, finish_row(M, K, S, first));
+}
+
+__global__ void __launch_bounds__(256)
+k_lm_finish(const int32_t* __restrict__ rows, const int32_t* __restrict__ count,
+            const WavePartial* __restrict__ partials, int V, RowOut out) {
+  const int k = blockIdx.x * 4 + threadIdx.x / kWave;
+  const int n = *count;
+  if (k >= n) return;
+  const LmWork w = lm_work(n, V);
+  const long long u0 = (long long)(k / w.pt) * w.nb;
+  const int n_split = lm_owner(w, u0 + w.nb - 1) - lm_owner(w, u0) + 1;
+  lm_finish_row(partials + (size_t)k * lm_stride(w), n_split, rows[k], out);
+}
+
+// the same for the streaming kernel's partials, n_split of every row
+__global__ void __launch_bounds__(256)
+k_lm_finish_n(const int32_t* __restrict__ rows, const int32_t* __restrict__ count,
+              const WavePartial* __restrict__ partials, int n_split, RowOut out) {
+  const int k = blockIdx.x * 4 + threadIdx.x / kWave;
+  if (k < *count) lm_finish_row(partials + (size_t)k * n_split, n_split, rows[k], out);
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-constexpr int kLmCUs = 256;   // compute units of the target
-
-// Parts of the hidden dimension for the streaming kernels: 1 (k_lm_stream)
-// up to kLsRows positions, 2 (k_lm_kstream) up to 2 kLsRows, when
-// a block is a whole number of 16-byte loads per thread and each wave's share
-// of the hidden operands fits its registers; 0: the tiled kernel.
-static int lm_kparts(long long n, int d) {
-  if (d > kLsMaxD) return 0;
-  if (n <= kLsRows) return d % 512 == 0 ? 1 : 0;
-  if (n <= 2 * kLsRows) return d % 1024 == 0 ? 2 : 0;
-  return 0;
-}
+// The streaming kernel serves at most kLsRows positions when a block is a
+// whole number of 16-byte loads per thread and each wave's share of the hidden
+// operands fits its registers; everything else the tiles.  At 32 positions of
+// d = 4096, V = 126464 the two take the same 163 us, at 8 positions of
+// d = 1024, V = 16000 15.5 us against 20.3 (a tile is 256 rows high, and a
+// workgroup's share of a small vocabulary is not); at 64 positions the tiles
+// take the 163 us of 32.
+static bool lm_streams(long long n, int d) { return n <= kLsRows && d % 512 == 0 && d <= kLsMaxD; }
 
 // the streaming kernel for d = 512 DM
 typedef void (*LmStreamFn)(const uint16_t*, const uint16_t*, const uint8_t*, const int32_t*,
@@ -945,75 +1132,31 @@ static const LmStreamFn kLmStream[kLsMaxD / 512] = {
     k_lm_stream<1>, k_lm_stream<2>, k_lm_stream<3>, k_lm_stream<4>,
     k_lm_stream<5>, k_lm_stream<6>, k_lm_stream<7>, k_lm_stream<8>};
 
-// the k-split kernel (S = 2) for d = 1024 i
-typedef void (*LmKStreamFn)(const uint16_t*, const uint16_t*, const uint8_t*, const int32_t*,
-                            const int32_t*, int, int, int, int32_t*, int32_t*, RowOut, float*);
-static const LmKStreamFn kLmKStream2[kLsMaxD / 1024] = {
-    k_lm_kstream<2, 2>, k_lm_kstream<4, 2>, k_lm_kstream<6, 2>, k_lm_kstream<8, 2>};
-constexpr int kKsSplits = 512;     // k_lm_ksum workgroups (vocabulary chunks)
-
 struct LmPlan {
-  int small;     // parts of the hidden dimension: 1 k_lm_stream, 2 k_lm_kstream; 0 tiled
-  int groups;    // k_lm_kstream: row-range groups (S groups workgroups)
-  int chunk;     // k_lm_ksum: vocabulary entries per workgroup
-  size_t off_plogits;
-  int m_tiles, n_tiles, n_split, tiles_per_split;
+  bool stream;   // k_lm_stream, not the tiles
+  int n_split;   // its workgroups
   size_t off_rows, off_partials, off_out, bytes;
 };
 
-// Row tiles cover the upper bound B*L (tiles past the device-side count exit
-// at once); the vocabulary is split so that about 512 workgroups run.
+// One workgroup per compute unit.  k_lm_stream: each a contiguous range of
+// row blocks; the tiles: as the number of candidates says, on the device
+// (lm_work).
 static LmPlan lm_plan(int B, int L, int d, int V, bool need_out) {
   LmPlan p{};
   const long long n = (long long)B * L;
-  const int S = lm_kparts(n, d);
-  if (S == 1) {
-    // one workgroup per compute unit, each a contiguous range of row blocks
-    p.small = 1;
-    const int nblk = (V + kLsBlk - 1) / kLsBlk;
-    p.n_split = nblk < kLmCUs ? nblk : kLmCUs;
-    p.off_rows = 256;
-    p.off_partials = p.off_rows + align256((size_t)n * 4);
-    p.off_out = p.off_partials + align256((size_t)n * p.n_split * sizeof(WavePartial));
-    p.bytes = p.off_out + (need_out ? 3 * align256((size_t)n * 4) : 0);
-    return p;
-  }
-  if (S > 1) {
-    // S workgroups (one per part) per row range, one workgroup per compute
-    // unit; the parts' logits of all 32 S positions in the workspace
-    p.small = S;
-    const int nblk = (V + 8 * S - 1) / (8 * S);
-    p.groups = nblk < kLmCUs / S ? nblk : kLmCUs / S;
-    p.chunk = (V + kKsSplits - 1) / kKsSplits;
-    p.n_split = (V + p.chunk - 1) / p.chunk;
-    p.off_rows = 256;
-    p.off_partials = p.off_rows + align256((size_t)n * 4);
-    p.off_plogits = p.off_partials + align256((size_t)n * p.n_split * sizeof(WavePartial));
-    p.off_out = p.off_plogits + align256((size_t)S * V * kLsRows * S * sizeof(float));
-    p.bytes = p.off_out + (need_out ? 3 * align256((size_t)n * 4) : 0);
-    return p;
-  }
-  p.m_tiles = (int)((n + kLmRows - 1) / kLmRows);
-  p.n_tiles = (V + kLmCols - 1) / kLmCols;
-  // one workgroup per CU at a time: pick the split with the shortest makespan
-  // (rounds of 256 workgroups x tiles per workgroup), fewer splits on ties
-  long long best = -1;
-  p.tiles_per_split = p.n_tiles;
-  for (int tps = 1; tps <= p.n_tiles; ++tps) {
-    const long long split = (p.n_tiles + tps - 1) / tps;
-    if (split > 65535) continue;
-    const long long rounds = ((long long)p.m_tiles * split + kLmCUs - 1) / kLmCUs;
-    const long long cost = rounds * tps;
-    if (best < 0 || cost < best) {
-      best = cost;
-      p.tiles_per_split = tps;
-    }
-  }
-  p.n_split = (p.n_tiles + p.tiles_per_split - 1) / p.tiles_per_split;
+  p.stream = lm_streams(n, d);
+  const int nblk = (V + kLsBlk - 1) / kLsBlk;
+  p.n_split = nblk < kLmGroups ? nblk : kLmGroups;
+  const size_t partials = p.stream ? (size_t)n * p.n_split : lm_max_partials(n);
   p.off_rows = 256;
   p.off_partials = p.off_rows + align256((size_t)n * 4);
-  p.off_out = p.off_partials + align256((size_t)n * p.n_split * sizeof(WavePartial));
+  p.off_out = p.off_partials + align256(partials * sizeof(WavePartial));
   p.bytes = p.off_out + (need_out ? 3 * align256((size_t)n * 4) : 0);
+  // the size that the interface states for these shapes (two halves of the
+  // hidden dimension, 64 float32 logits per vocabulary entry each); the tiles
+  // use the front of it
+  if (n > kLsRows && n <= 64 && d % 1024 == 0 && d <= kLsMaxD)
+    p.bytes += align256((size_t)2 * V * 64 * sizeof(float));
   return p;
 }
 
@@ -1035,14 +1178,20 @@ static hipError_t lm_allow_lds() {
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < kLmMaxDevices && lm_lds_allowed[dev].load(std::memory_order_acquire))
     return hipSuccess;
-  hipError_t a = hipFuncSetAttribute((const void*)k_lm_partial,
+  hipError_t a = hipFuncSetAttribute((const void*)k_lm_narrow<true>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLmLdsBytes);
+  if (a == hipSuccess)
+    a = hipFuncSetAttribute((const void*)k_lm_narrow<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kLmLdsBytes);
+  if (a == hipSuccess)
+    a = hipFuncSetAttribute((const void*)k_lm_wide<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kLmLdsBytes);
+  if (a == hipSuccess)
+    a = hipFuncSetAttribute((const void*)k_lm_wide<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kLmLdsBytes);
   for (int i = 0; i < kLsMaxD / 512 && a == hipSuccess; ++i)
     a = hipFuncSetAttribute((const void*)kLmStream[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)kLsLdsBytes(512 * (i + 1)));
-  for (int i = 0; i < kLsMaxD / 1024 && a == hipSuccess; ++i)
-    a = hipFuncSetAttribute((const void*)kLmKStream2[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)ks_lds_bytes<2>(1024 * (i + 1)));
   if (a == hipSuccess && dev >= 0 && dev < kLmMaxDevices)
     lm_lds_allowed[dev].store(true, std::memory_order_release);
   return a;
@@ -1056,33 +1205,39 @@ static hipError_t lm_launch(const void* hidden, const void* weight, int B, int L
   WavePartial* part = (WavePartial*)(ws + p.off_partials);
   const hipError_t attr = lm_allow_lds();
   if (attr != hipSuccess) return attr;
-  if (p.small > 1) {
-    // the k-split kernel compacts the candidates itself
-    const uint16_t* h = (const uint16_t*)hidden;
-    const uint16_t* w = (const uint16_t*)weight;
-    float* plog = (float*)(ws + p.off_plogits);
-    const dim3 grid((unsigned)(p.groups * 2)), block(kKsWaves * kWave);
-    hipLaunchKernelGGL(kLmKStream2[d / 1024 - 1], grid, block, ks_lds_bytes<2>(d), st, h, w, mask, bs,
-                       be, B, L, V, rows, count, out, plog);
-    hipLaunchKernelGGL(k_lm_ksum<2>, dim3((unsigned)p.n_split), dim3(256), 0, st, plog, count, V,
-                       p.chunk, part, p.n_split);
-  } else if (p.small) {
+  const long long n = (long long)B * L;
+  if (p.stream) {
     // the streaming kernel compacts the candidates itself
     hipLaunchKernelGGL(kLmStream[d / 512 - 1], dim3((unsigned)p.n_split), dim3(kLsWaves * kWave),
                        kLsLdsBytes(d), st, (const uint16_t*)hidden, (const uint16_t*)weight, mask,
                        bs, be, B, L, V, rows, count, out, part, p.n_split);
+    hipLaunchKernelGGL(k_lm_finish_n, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, rows, count,
+                       part, p.n_split, out);
   } else {
-    hipLaunchKernelGGL(k_lm_zero, dim3(1), dim3(64), 0, st, count);
-    hipLaunchKernelGGL(k_lm_compact, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, st, mask, bs, be,
-                       B, L, rows, count, out);
-    hipLaunchKernelGGL(k_lm_partial, dim3((unsigned)p.m_tiles, (unsigned)p.n_split),
-                       dim3(kLmThreads), kLmLdsBytes, st, (const uint16_t*)hidden,
-                       (const uint16_t*)weight, rows, count, d, V, p.tiles_per_split,
-                       (uint32_t)((size_t)B * L * d * 2), part, p.n_split);
+    const LmArgs a{(const uint16_t*)hidden, (const uint16_t*)weight, rows, count, part, d, V,
+                   (uint32_t)((size_t)B * L * d * 2)};
+    const LmCand c{mask, bs, be, B, L, out};
+    const dim3 grid(kLmGroups), block(kLmThreads);
+    if (n <= kLmSelf) {
+      hipLaunchKernelGGL(k_lm_narrow<true>, grid, block, kLmLdsBytes, st, a, c);
+    } else {
+      if (n <= kLmOneWg) {
+        hipLaunchKernelGGL(k_lm_compact_one, dim3(1), dim3(kLmOneThreads), 0, st, mask, bs, be, B, L,
+                           rows, count, out);
+      } else {
+        hipLaunchKernelGGL(k_lm_zero, dim3(1), dim3(64), 0, st, count);
+        hipLaunchKernelGGL(k_lm_compact, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, st, mask, bs, be,
+                           B, L, rows, count, out);
+      }
+      hipLaunchKernelGGL(k_lm_narrow<false>, grid, block, kLmLdsBytes, st, a, c);
+    }
+    // the host knows the span, the device the candidates: the kernels whose
+    // range the number is not in return at once
+    if (n > kLmNarrow) hipLaunchKernelGGL(k_lm_wide<true>, grid, block, kLmLdsBytes, st, a);
+    if (n > kLmMaxPt) hipLaunchKernelGGL(k_lm_wide<false>, grid, block, kLmLdsBytes, st, a);
+    hipLaunchKernelGGL(k_lm_finish, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, rows, count, part,
+                       V, out);
   }
-  const long long n = (long long)B * L;
-  hipLaunchKernelGGL(k_lm_finish, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, rows, count,
-                     part, p.n_split, out);
   return hipGetLastError();
 }
 

@@ -204,3 +204,61 @@ def test_lmhead_rejects_bad_shapes(gpu):
     with pytest.raises(gpu.FdllmError):
         gpu.fdllm_lmhead_confidence(hidden, weight, m, s, e, *out,
                                     workspace=torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+
+
+# (B, L, candidates, d, V): the tile widths and their edges, one and several
+# position tiles, each way the candidates are listed (up to 2048 positions, up
+# to 8192, more), vocabularies of less than a row a workgroup, of part of a
+# tile and of several, hidden sizes whose 16-stage blocks are exchanged between
+# workgroups (multiples of 2048) and not
+TILE_CASES = [
+    (1, 40, 1, 2048, 300), (2, 40, 32, 2048, 5000), (8, 256, 33, 4096, 4099), (2, 40, 64, 192, 70001),
+    (8, 64, 65, 2048, 4100), (4, 300, 128, 512, 2000), (8, 256, 129, 256, 9000), (8, 64, 192, 4096, 700),
+    (1, 300, 193, 128, 66000), (16, 16, 256, 1024, 1000), (16, 32, 257, 192, 4097), (20, 32, 384, 64, 7000),
+    (10, 60, 513, 128, 300), (48, 50, 1500, 64, 5003), (130, 64, 40, 256, 1000), (130, 64, 300, 256, 3000),
+    (64, 33, 127, 64, 15), (4, 32, 100, 2048, 40000),
+]
+
+
+@pytest.mark.parametrize("B,L,n,d,V", TILE_CASES)
+def test_lmhead_tile_widths(gpu, B, L, n, d, V):
+    """n candidates spread over the span, exact logits: tokens, conf, eps, lse of every row."""
+    say(f"[lmhead tiles] B={B} L={L} candidates={n} d={d} V={V}")
+    hidden, weight, _, _, _, _, _ = _case(B, L, d, V, "exact", L, seed=n + d)
+    g = torch.Generator().manual_seed(n)
+    mask = torch.zeros(B * L, dtype=torch.uint8)
+    mask[torch.randperm(B * L, generator=g)[:n]] = 1
+    mask = mask.view(B, L)
+    start = torch.zeros(B, dtype=torch.int32)
+    end = torch.full((B,), L, dtype=torch.int32)
+    out = [t.cpu().numpy() for t in _gpu_conf(gpu, hidden, weight, mask.cuda(), start.cuda(), end.cuda())]
+    cells = candidates(mask.numpy(), start.numpy(), end.numpy(), range(B))
+    assert len(cells) == n
+    check_defaults(*out, mask.numpy(), start.numpy(), end.numpy(), range(B))
+    lg, _, _ = _oracle_rows(hidden, weight, cells)
+    for b, i in cells:
+        t, c, ep, lse = oracle.position_confidence(lg[(b, i)])
+        assert int(out[0][b, i]) == t, (b, i, int(out[0][b, i]), t)
+        de = abs(float(out[2][b, i]) - ep)
+        assert abs(float(out[1][b, i]) - c) <= CONF_RTOL * c, (b, i)
+        assert de <= max(1e-5 * ep, EPS_ATOL_LMHEAD), (b, i, de, ep)
+        assert abs(float(out[3][b, i]) - lse) <= CONF_RTOL * max(abs(lse), 1.0), (b, i)
+
+
+@pytest.mark.parametrize("B,L,d,V", [(1, 32, 4096, 40000), (2, 32, 4096, 40000), (4, 32, 2048, 40000),
+                                     (6, 32, 4096, 20000), (12, 32, 1024, 9000)])
+def test_lmhead_equal_weight_rows_tie(gpu, B, L, d, V):
+    """General values, every weight row twice: the two logits are the same bits
+    wherever the rows sit, so the token is the lower of the two."""
+    say(f"[lmhead equal rows] B={B} L={L} d={d} V={V}")
+    g = torch.Generator().manual_seed(d + V)
+    half = torch.randn((V // 2, d), generator=g) / d ** 0.5
+    weight = torch.cat([half, half]).to(torch.bfloat16).cuda()
+    target = torch.randint(0, V // 2, (B, L), generator=g)
+    hidden = (12.0 * half[target] / half[target].square().sum(-1, keepdim=True)
+              + torch.randn((B, L, d), generator=g)).to(torch.bfloat16).cuda()
+    mask = torch.ones((B, L), dtype=torch.uint8, device="cuda")
+    start = torch.zeros(B, dtype=torch.int32, device="cuda")
+    end = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    tok = _gpu_conf(gpu, hidden, weight, mask, start, end)[0].cpu()
+    assert torch.equal(tok, target.to(torch.int32))
