@@ -29,6 +29,17 @@ constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u;   // Philox4x32 multipl
 constexpr uint32_t kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;   // Philox4x32 key increments
 constexpr uint32_t kTokC0 = 0xFFFFFFFFu, kTokC3 = 0xFFFFFFFFu, kHeightC0 = 0xFFFFFFFEu;
 
+// a ^ b ^ c in one instruction (truth table 0x96)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// One round's multiplications are 32 x 32 -> 64 bits; each is one
+// v_mad_u64_u32, not a v_mul_lo and a v_mul_hi.  Row: all four counter words
+// are the same for the whole wave (the scalar unit's work); otherwise the
+// first one alone differs, and what the first round makes of the other three
+// is the wave's too.
+template <bool Row>
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
@@ -36,73 +47,88 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
       k0 += kW0;
       k1 += kW1;
     }
-    const uint32_t hi0 = __umulhi(kM0, c[0]), lo0 = kM0 * c[0];
-    const uint32_t hi1 = __umulhi(kM1, c[2]), lo1 = kM1 * c[2];
-    const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
+    const uint64_t p0 = (uint64_t)kM0 * c[0], p1 = (uint64_t)kM1 * c[2];
+    const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+    const uint32_t n0 = Row || r == 0 ? h1 ^ c[1] ^ k0 : xor3(h1, c[1], k0);
+    const uint32_t n2 = Row ? h0 ^ c[3] ^ k1 : xor3(h0, c[3], k1);
+    c[1] = (uint32_t)p1;
+    c[3] = (uint32_t)p0;
     c[0] = n0;
-    c[1] = lo1;
     c[2] = n2;
-    c[3] = lo0;
   }
 }
 
-__device__ __forceinline__ uint16_t bf16_rne(float f) {
+__device__ __forceinline__ uint32_t bf16_rne(float f) {
   const uint32_t u = __float_as_uint(f);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
+// (the sum of w's bytes - 510) / 128: an integer of at most 10 bits times a
+// power of two, exact whatever the order of the two operations
 __device__ __forceinline__ float background(uint32_t w) {
-  const int s = (int)(w & 0xFFu) + (int)((w >> 8) & 0xFFu) + (int)((w >> 16) & 0xFFu) + (int)(w >> 24);
-  return __fmul_rn((float)(s - 510), 0.0078125f);   // exact: |s - 510| <= 510
+  const uint32_t s = __builtin_amdgcn_sad_u8(w, 0u, 0u);
+  return __builtin_fmaf((float)s, 0.0078125f, -3.984375f);
 }
 
 // Logits rows of every sequence's active block at step t.  One row per
 // blockIdx.x (b = x / blk, slot = x % blk); blockIdx.y covers the vocabulary
-// in groups of 4 entries per thread (one Philox call each).
-__global__ void __launch_bounds__(256)
+// in runs of kSynthRun entries, a thread 8 entries (two Philox calls, whose
+// rounds overlap) per trip.
+// Bound by the ALUs: a Philox call is 18 64-bit multiplications beyond the
+// row's own (the compiler forms what does not depend on the entry on the
+// scalar unit, the spike's token and height among it, so no thread waits for
+// another) and 20 three-way exclusive ors for four entries.  8 x 32 rows at
+// V = 126464: 41.6 -> 21.6 us (65 MB written).
+constexpr int kSynthThreads = 256;
+constexpr int kSynthTrips = 4;
+constexpr int kSynthRun = kSynthThreads * 8 * kSynthTrips;
+
+__global__ void __launch_bounds__(kSynthThreads)
 k_synth(uint16_t* __restrict__ logits, int B, int L, int V, int blk,
         const int32_t* __restrict__ bstart, const int32_t* __restrict__ bend, uint32_t k0,
         uint32_t k1, const int32_t* __restrict__ step_dev, int step_host,
         const int32_t* __restrict__ active) {
-  __shared__ int s_tok;
-  __shared__ float s_h;
   if (active && *active == 0) return;
   const int b = blockIdx.x / blk;
-  const int i = bstart[b] + blockIdx.x % blk;
-  const int e = bend[b];
-  if (bstart[b] < 0 || e > L || i >= e) return;
+  const int s = bstart[b], e = bend[b];
+  const int i = s + (int)(blockIdx.x % blk);
+  if (s < 0 || e > L || i >= e) return;
   const uint32_t t = (uint32_t)(step_dev ? *step_dev : step_host);
-  if (threadIdx.x == 0) {
-    uint32_t c[4] = {kTokC0, (uint32_t)i, (uint32_t)b, kTokC3};
-    philox4x32_10(c, k0, k1);
-    s_tok = (int)(c[0] % (uint32_t)V);
-    uint32_t y[4] = {kHeightC0, (uint32_t)i, (uint32_t)b, t};
-    philox4x32_10(y, k0, k1);
-    const float u1 = __fmul_rn((float)(y[0] >> 8), 5.9604644775390625e-08f);   // 2^-24
-    const float u2 = __fmul_rn((float)(y[1] >> 8), 5.9604644775390625e-08f);
-    const float six_u2 = __fmul_rn(6.0f, u2);
-    s_h = u1 < 0.6f ? __fadd_rn(8.0f, six_u2) : six_u2;
-  }
-  __syncthreads();
-  const int q = blockIdx.y * blockDim.x + threadIdx.x;   // vocabulary group
-  const int v0 = 4 * q;
-  if (v0 >= V) return;
-  uint32_t c[4] = {(uint32_t)q, (uint32_t)i, (uint32_t)b, t};
-  philox4x32_10(c, k0, k1);
-  uint16_t out[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float x = background(c[j]);
-    if (v0 + j == s_tok) x = __fadd_rn(x, s_h);
-    out[j] = bf16_rne(x);
-  }
+  uint32_t y[4] = {kTokC0, (uint32_t)i, (uint32_t)b, kTokC3};
+  philox4x32_10<true>(y, k0, k1);
+  const uint32_t tok = y[0] % (uint32_t)V;
+  uint32_t z[4] = {kHeightC0, (uint32_t)i, (uint32_t)b, t};
+  philox4x32_10<true>(z, k0, k1);
+  const float u1 = __fmul_rn((float)(z[0] >> 8), 5.9604644775390625e-08f);   // 2^-24
+  const float u2 = __fmul_rn((float)(z[1] >> 8), 5.9604644775390625e-08f);
+  const float six_u2 = __fmul_rn(6.0f, u2);
+  const float h = u1 < 0.6f ? __fadd_rn(8.0f, six_u2) : six_u2;
   uint16_t* row = logits + ((size_t)b * L + i) * (size_t)V;
-  if (v0 + 4 <= V && ((((uintptr_t)(row + v0)) & 7u) == 0)) {
-    const uint2 packed = make_uint2((uint32_t)out[0] | ((uint32_t)out[1] << 16),
-                                    (uint32_t)out[2] | ((uint32_t)out[3] << 16));
-    *reinterpret_cast<uint2*>(row + v0) = packed;
-  } else {
-    for (int j = 0; j < 4 && v0 + j < V; ++j) row[v0 + j] = out[j];
+  // a row starts on a 2-byte boundary; 16-byte stores where it allows them
+  const bool wide = ((uintptr_t)row & 15u) == 0;
+#pragma unroll 1
+  for (int trip = 0; trip < kSynthTrips; ++trip) {
+    const uint32_t v0 = blockIdx.y * kSynthRun + (uint32_t)(trip * kSynthThreads + (int)threadIdx.x) * 8u;
+    if (v0 >= (uint32_t)V) return;
+    const uint32_t q = v0 / 4u;                 // vocabulary group of four
+    uint32_t c[2][4] = {{q, (uint32_t)i, (uint32_t)b, t}, {q + 1u, (uint32_t)i, (uint32_t)b, t}};
+    philox4x32_10<false>(c[0], k0, k1);
+    philox4x32_10<false>(c[1], k0, k1);
+    uint32_t out[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float lo = background(c[j / 2][2 * (j % 2)]), hi = background(c[j / 2][2 * (j % 2) + 1]);
+      if (v0 + 2u * j == tok) lo = __fadd_rn(lo, h);
+      if (v0 + 2u * j + 1u == tok) hi = __fadd_rn(hi, h);
+      out[j] = bf16_rne(lo) | (bf16_rne(hi) << 16);
+    }
+    if (wide && v0 + 8u <= (uint32_t)V) {
+      *reinterpret_cast<uint4*>(row + v0) = make_uint4(out[0], out[1], out[2], out[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (v0 + j < (uint32_t)V) row[v0 + j] = (uint16_t)(out[j / 2] >> (16 * (j % 2)));
+    }
   }
 }
 
@@ -113,18 +139,11 @@ struct GenState {
   int32_t pad;
 };
 
-// One wavefront per sequence: advance to the first block, from the current
-// one on, that still has a masked position.  Optionally records this step's
-// n_commit and counts the sequences left active.
-__global__ void __launch_bounds__(256)
-k_advance(const uint8_t* __restrict__ mask, int32_t* __restrict__ bstart,
-          int32_t* __restrict__ bend, int B, int G, int blk, GenState* st,
-          const int32_t* __restrict__ n_commit, int32_t* __restrict__ hist, int hist_steps,
-          int32_t* __restrict__ n_active) {
-  const int lane = threadIdx.x % kWave;
-  const int b = blockIdx.x * 4 + threadIdx.x / kWave;
-  if (b >= B) return;
-  const bool worked = st == nullptr || st->active > 0;
+// Advances sequence b to the first block, from the current one on, that
+// still has a masked position (one wavefront); true while there is one.
+__device__ __forceinline__ bool advance_one(const uint8_t* __restrict__ mask,
+                                            int32_t* __restrict__ bstart, int32_t* __restrict__ bend,
+                                            int b, int G, int blk, int lane) {
   int s = bstart[b];
   if (s < 0 || s > G) s = G;
   while (s < G) {
@@ -134,16 +153,60 @@ k_advance(const uint8_t* __restrict__ mask, int32_t* __restrict__ bstart,
     if (__ballot(any) != 0ull) break;
     s += blk;
   }
+  if (lane == 0) {
+    bstart[b] = s < G ? s : G;
+    bend[b] = s < G && s + blk < G ? s + blk : G;
+  }
+  return s < G;
+}
+
+// One wavefront per sequence.  Optionally records this step's n_commit and
+// counts the sequences left active.
+__global__ void __launch_bounds__(256)
+k_advance(const uint8_t* __restrict__ mask, int32_t* __restrict__ bstart,
+          int32_t* __restrict__ bend, int B, int G, int blk, GenState* st,
+          const int32_t* __restrict__ n_commit, int32_t* __restrict__ hist, int hist_steps,
+          int32_t* __restrict__ n_active) {
+  const int lane = threadIdx.x % kWave;
+  const int b = blockIdx.x * 4 + threadIdx.x / kWave;
+  if (b >= B) return;
+  const bool worked = st == nullptr || st->active > 0;
+  const bool left = advance_one(mask, bstart, bend, b, G, blk, lane);
   if (lane != 0) return;
   if (st && hist && worked && st->t < hist_steps) hist[(size_t)st->t * B + b] = n_commit[b];
-  if (s < G) {
-    bstart[b] = s;
-    bend[b] = s + blk < G ? s + blk : G;
+  if (left) {
     if (st) atomicAdd(&st->active_next, 1);
     if (n_active) atomicAdd(n_active, 1);
-  } else {
-    bstart[b] = G;
-    bend[b] = G;
+  }
+}
+
+// The same for a small batch in one workgroup, which then also closes the
+// step (k_step_end's work): a launch less per step.  Up to kCloseMaxB
+// sequences, four a wave; beyond it the waves' turns would cost more than
+// the launch.
+constexpr int kCloseWaves = 16;
+constexpr int kCloseMaxB = 4 * kCloseWaves;
+
+__global__ void __launch_bounds__(kCloseWaves * kWave)
+k_advance_close(const uint8_t* __restrict__ mask, int32_t* __restrict__ bstart,
+                int32_t* __restrict__ bend, int B, int G, int blk, GenState* st,
+                const int32_t* __restrict__ n_commit, int32_t* __restrict__ hist, int hist_steps) {
+  __shared__ int s_left;
+  const int lane = threadIdx.x % kWave;
+  const int active = st->active, t = st->t;
+  if (threadIdx.x == 0) s_left = 0;
+  __syncthreads();
+  for (int b = threadIdx.x / kWave; b < B; b += kCloseWaves) {
+    const int32_t n = lane == 0 ? n_commit[b] : 0;
+    const bool left = advance_one(mask, bstart, bend, b, G, blk, lane);
+    if (lane != 0) continue;
+    if (hist && active > 0 && t < hist_steps) hist[(size_t)t * B + b] = n;
+    if (left) atomicAdd(&s_left, 1);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (active > 0) st->t = t + 1;
+    st->active = s_left;
   }
 }
 
@@ -182,6 +245,10 @@ k_init(uint8_t* __restrict__ mask, int32_t* __restrict__ x, int32_t* __restrict_
   }
 }
 
+dim3 synth_grid(int B, int blk, int V) {
+  return dim3((unsigned)(B * blk), (unsigned)((V - 1) / kSynthRun + 1));
+}
+
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 bool desc_ok(const fdllm_generation_desc* d) {
@@ -211,10 +278,9 @@ struct fdllm_generation_s {
 static fdllm_status enqueue_steps(fdllm_generation g, int steps, hipStream_t s) {
   const fdllm_generation_desc& d = g->d;
   const uint32_t k0 = (uint32_t)(d.seed & 0xFFFFFFFFull), k1 = (uint32_t)(d.seed >> 32);
-  const int nq = (d.V + 3) / 4;
-  const dim3 sgrid((unsigned)(d.B * d.blk), (unsigned)((nq + 255) / 256));
+  const dim3 sgrid = synth_grid(d.B, d.blk, d.V);
   for (int k = 0; k < steps; ++k) {
-    hipLaunchKernelGGL(k_synth, sgrid, dim3(256), 0, s, (uint16_t*)d.logits, d.B, d.G, d.V, d.blk,
+    hipLaunchKernelGGL(k_synth, sgrid, dim3(kSynthThreads), 0, s, (uint16_t*)d.logits, d.B, d.G, d.V, d.blk,
                        d.block_start, d.block_end, k0, k1, &g->st->t, 0, &g->st->active);
     if (hipGetLastError() != hipSuccess) return FDLLM_ERR_HIP;
     const fdllm_status st = fdllm_decode_step(
@@ -222,10 +288,16 @@ static fdllm_status enqueue_steps(fdllm_generation g, int steps, hipStream_t s) 
         d.param, d.eta, d.eta_uniform, nullptr, nullptr, nullptr, nullptr, nullptr, g->n_commit,
         g->step_ws, g->step_ws_bytes, (fdllm_stream)s);
     if (st != FDLLM_OK) return st;
-    hipLaunchKernelGGL(k_advance, dim3((unsigned)((d.B + 3) / 4)), dim3(256), 0, s, d.mask,
-                       d.block_start, d.block_end, d.B, d.G, d.blk, g->st, g->n_commit,
-                       d.n_commit_hist, d.max_steps, (int32_t*)nullptr);
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, g->st);
+    if (d.B <= kCloseMaxB) {
+      hipLaunchKernelGGL(k_advance_close, dim3(1), dim3(kCloseWaves * kWave), 0, s, d.mask,
+                         d.block_start, d.block_end, d.B, d.G, d.blk, g->st, g->n_commit,
+                         d.n_commit_hist, d.max_steps);
+    } else {
+      hipLaunchKernelGGL(k_advance, dim3((unsigned)((d.B + 3) / 4)), dim3(256), 0, s, d.mask,
+                         d.block_start, d.block_end, d.B, d.G, d.blk, g->st, g->n_commit,
+                         d.n_commit_hist, d.max_steps, (int32_t*)nullptr);
+      hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, g->st);
+    }
     if (hipGetLastError() != hipSuccess) return FDLLM_ERR_HIP;
   }
   return FDLLM_OK;
@@ -241,8 +313,7 @@ fdllm_status fdllm_synth_logits(void* logits, int B, int L, int V, int blk,
   if (B == 0) return FDLLM_OK;
   if (!logits || !block_start || !block_end) return FDLLM_ERR_INVALID_ARG;
   if ((long long)B * blk > 0x7fffffffLL) return FDLLM_ERR_SIZE;
-  const int nq = (V + 3) / 4;
-  hipLaunchKernelGGL(k_synth, dim3((unsigned)(B * blk), (unsigned)((nq + 255) / 256)), dim3(256), 0,
+  hipLaunchKernelGGL(k_synth, synth_grid(B, blk, V), dim3(kSynthThreads), 0,
                      (hipStream_t)stream, (uint16_t*)logits, B, L, V, blk, block_start, block_end,
                      (uint32_t)(seed & 0xFFFFFFFFull), (uint32_t)(seed >> 32),
                      (const int32_t*)nullptr, step, (const int32_t*)nullptr);

@@ -145,3 +145,37 @@ def test_generation_graph_equals_eager(gpu, B, G, blk, V):
     say(f"  {sa} steps, {B * G / sa:.2f} tokens per step")
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("V", [1, 7, 8, 9, 8191, 8192, 8193, 16390])
+def test_synth_logits_edges(gpu, V):
+    """Rows shorter and longer than a thread's 8 entries and a workgroup's
+    8192, on every 2-byte alignment of the row start; nothing past the row."""
+    B, L, blk, seed, step = 2, 9, 9, 77, 3
+    logits = torch.empty((B, L, V), dtype=torch.bfloat16, device="cuda")
+    logits.view(torch.int16).fill_(BF16_SENTINEL)
+    start = torch.tensor([0, 2], dtype=torch.int32, device="cuda")
+    end = torch.tensor([8, 9], dtype=torch.int32, device="cuda")
+    say(f"[synth edges] V={V}")
+    gpu.fdllm_synth_logits(logits, start, end, blk, seed, step)
+    torch.cuda.synchronize()
+    got = logits.view(torch.int16).cpu().numpy().view(np.uint16)
+    for b, (s, e) in enumerate([(0, 8), (2, 9)]):
+        for i in range(L):
+            if s <= i < e:
+                assert np.array_equal(got[b, i], synth.row_bits(seed, b, i, step, V)), (b, i)
+            else:
+                assert (got[b, i] == BF16_SENTINEL).all(), (b, i)
+
+
+@pytest.mark.parametrize("B,use_graph", [(1, True), (17, False), (64, True), (65, True)])
+def test_generation_step_close_sizes(gpu, B, use_graph):
+    """The step closed by one workgroup (up to 64 sequences, four a wave) and
+    by a kernel of its own: steps, history and tokens against the oracle."""
+    G, blk, V, seed = 12, 4, 64, 5
+    say(f"[generation step close] B={B}")
+    gen = gpu.Generation(B, G, blk, V, seed, "factor", 1.0, chunk=3, use_graph=use_graph)
+    steps = gen.run()
+    torch.cuda.synchronize()
+    _replay(seed, B, G, blk, V, "factor", 1.0, None, gen.hist.cpu().numpy(), steps, gen.x.cpu().numpy())
+    gen.close()
