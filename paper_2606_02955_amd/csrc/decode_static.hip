@@ -67,7 +67,12 @@ extern "C" fdllm_status fdllm_decode_step_static(
     return FDLLM_ERR_INVALID_ARG;
   if (!(eta_uniform == eta_uniform)) return FDLLM_ERR_INVALID_ARG;
   if (B > 0 && (!logits || !mask || !block_start || !block_end || !x)) return FDLLM_ERR_INVALID_ARG;
-  if (need > (size_t)FDLLM_STATIC_SCRATCH_BYTES) return FDLLM_ERR_SCRATCH;
+  if (need > (size_t)FDLLM_STATIC_SCRATCH_BYTES) {
+    // a large batch's workspace only holds the outputs the caller does not
+    // take; without it the step runs in one kernel, with the same bits
+    if (!fdllm::workspace_optional(B)) return FDLLM_ERR_SCRATCH;
+    need = 0;
+  }
   void* ws = nullptr;
   if (need > 0 && B > 0) {
     ws = scratch_on_current_device(&st);

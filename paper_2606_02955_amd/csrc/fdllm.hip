@@ -45,6 +45,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "fdllm.h"
@@ -69,6 +70,9 @@
 #endif
 #ifndef FDLLM_FUSED_MIN_B
 #define FDLLM_FUSED_MIN_B 256     // batches from this size run one workgroup per sequence
+#endif
+#ifndef FDLLM_ROWS_MAX_B
+#define FDLLM_ROWS_MAX_B 768      // and below this share their rows evenly instead, where they can
 #endif
 #ifndef FDLLM_GROUPS32_MIN_B
 #define FDLLM_GROUPS32_MIN_B 8    // small batches from this size: 32 row groups per sequence, not 64
@@ -170,7 +174,7 @@ constexpr int kAcc = 4;   // independent double accumulators per lane
 // is 64 consecutive vectors); lane l reads vector k*64 + l.
 template <class Vec, int U, int S>
 __device__ __forceinline__ WavePartial row_pass(const typename Vec::Raw* __restrict__ row, int nvec, int w,
-                                                typename Vec::Raw* __restrict__ kept) {
+                                                typename Vec::Raw* kept, typename Vec::Raw* unkept) {
   using Raw = typename Vec::Raw;
   constexpr int E = Vec::kElems;
   const int lane = lane_id();
@@ -188,11 +192,12 @@ __device__ __forceinline__ WavePartial row_pass(const typename Vec::Raw* __restr
   // without one element equal to m (so no sum ever holds the lane maximum)
   double acc = 0.0, pend = 0.0;
   // the batch in which this lane's maximum first appeared, and its vectors,
-  // kept in this wave's LDS area `kept` (2 U kWave vectors): every batch is
-  // written there, a lane whose maximum grows into slot 0 (u kWave + lane),
-  // the others into slot 1, so no per-lane select is needed; the lowest index
-  // of the row maximum is found there at the end (a re-read from memory
-  // would cost a dependent HBM latency per row)
+  // kept in this wave's LDS area `kept` (U kWave vectors): every batch is
+  // written to LDS, by a lane whose maximum grows into that area (u kWave +
+  // lane), by the others into `unkept`, which nobody reads (waves may share
+  // it), so no per-lane select is needed; the lowest index of the row maximum
+  // is found there at the end (a re-read from memory would cost a dependent
+  // HBM latency per row)
   int rec = -1;
 
   // sum of a batch's terms: kAcc accumulators, each started from its first
@@ -218,7 +223,7 @@ __device__ __forceinline__ WavePartial row_pass(const typename Vec::Raw* __restr
       for (int e = 0; e < E; ++e) bm = fmaxf(bm, x[u][e]);
     const bool grows = bm > m;
     rec = grows ? batch : rec;
-    Raw* const dst = kept + (grows ? 0 : U * kWave) + lane;
+    Raw* const dst = (grows ? kept : unkept) + lane;
 #pragma unroll
     for (int u = 0; u < U; ++u) dst[u * kWave] = r[u];
     const float mn = fmaxf(m, bm);
@@ -426,7 +431,7 @@ k_confidence(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
              const int32_t* __restrict__ bend, RowOut out) {
   using Shape = SplitShape<S>;
   __shared__ WavePartial part[Shape::kWaves];
-  __shared__ typename Vec::Raw s_kept[2 * U * Shape::kThreads];
+  __shared__ typename Vec::Raw s_kept[U * (Shape::kThreads + kWave)];
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   const int rloc = wave / S;
@@ -461,7 +466,9 @@ k_confidence(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
     const size_t slot = row0 + (size_t)(s + rel);
     const bool cand = inwin && mask[slot] != 0;
     WavePartial wp{};
-    if (cand) wp = row_pass<Vec, U, S>(logits + (long long)slot * nvec, nvec, w, s_kept + wave * 2 * U * kWave);
+    if (cand)
+      wp = row_pass<Vec, U, S>(logits + (long long)slot * nvec, nvec, w, s_kept + wave * U * kWave,
+                               s_kept + Shape::kWaves * U * kWave);
     if constexpr (S > 1) {
       if (lane == 0) part[wave] = wp;
       __syncthreads();
@@ -493,7 +500,7 @@ k_confidence_parts(const typename Vec::Raw* __restrict__ logits, int B, int L, i
                    const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
                    const int32_t* __restrict__ bend, RowOut out, WavePartial* __restrict__ parts) {
   constexpr int P = S / 4;                                  // workgroups per slot
-  __shared__ typename Vec::Raw s_kept[2 * U * 256];
+  __shared__ typename Vec::Raw s_kept[U * (256 + kWave)];
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   const long long slot = blockIdx.x / P;
@@ -507,7 +514,8 @@ k_confidence_parts(const typename Vec::Raw* __restrict__ logits, int B, int L, i
     if (w == 0 && lane == 0) store_default(out, (size_t)slot);
     return;
   }
-  const WavePartial wp = row_pass<Vec, U, S>(logits + slot * (long long)nvec, nvec, w, s_kept + wave * 2 * U * kWave);
+  const WavePartial wp = row_pass<Vec, U, S>(logits + slot * (long long)nvec, nvec, w, s_kept + wave * U * kWave,
+                                             s_kept + U * 256);
   if (lane == 0) parts[slot * S + w] = wp;
 }
 
@@ -908,6 +916,9 @@ __global__ void __launch_bounds__(NT) k_select_wide(SelectIO io, int B, int L, f
 // ---------------------------------------------------------------------------
 // kernel: fused decode step, one workgroup of W waves per sequence
 // ---------------------------------------------------------------------------
+// Each wave has an `unkept` area of its own: one for all (38 KiB of LDS a
+// workgroup, not 65) measured 1024 blocks of one to three candidates 136 ->
+// 164 us, and so did letting the waves without a row leave early (139 to 147).
 template <class Vec, int U, int W, int R, bool Robust>
 __global__ void __launch_bounds__(W * kWave)
 #if FDLLM_WAVES_PER_EU > 0
@@ -950,7 +961,8 @@ k_fused(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
   for (int c = wave; c < m; c += W) {
     const int slot = s_cand[c];
     const size_t r = row0 + s + slot;
-    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, s_kept + wave * 2 * U * kWave);
+    typename Vec::Raw* kept = s_kept + wave * 2 * U * kWave;
+    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, kept, kept + U * kWave);
     const RowResult rr = finish_row_x(wp.m, wp.K, wp.S, wp.first);
     if (lane == 0) {
       store_row(out, r, rr);
@@ -1022,7 +1034,8 @@ k_fused_wide(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
   for (int c = wave; c < m; c += W) {
     const int slot = s_cand[c];
     const size_t r = row0 + s + slot;
-    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, s_kept + wave * 2 * U * kWave);
+    typename Vec::Raw* kept = s_kept + wave * 2 * U * kWave;
+    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, kept, kept + U * kWave);
     const RowResult rr = finish_row_x(wp.m, wp.K, wp.S, wp.first);
     if (lane == 0) {
       store_row(out, r, rr);
@@ -1082,6 +1095,175 @@ k_fused_wide(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
   if (n_commit && tid == 0) n_commit[b] = nstar;
 }
 
+// ---------------------------------------------------------------------------
+// kernel: the vocabulary pass of a large batch, the candidate rows shared
+// evenly by all waves of the chip
+// ---------------------------------------------------------------------------
+// k_fused gives a sequence to a workgroup, so with few sequences per CU it
+// takes as long as the CU whose sequences have the most candidates: a wave
+// takes a row of V = 126464 in 37 us of arithmetic, alone or beside three
+// others, and the waves of another CU cannot help.  Here one workgroup of
+// kRowsWaves waves per CU finds every sequence's candidates (64 positions a
+// ballot; the words, their running counts and first slots in LDS), and
+// workgroup g of n takes the rows [g T / n, (g + 1) T / n) of all T, each as
+// k_fused would, with the same bits.  The selection follows as a launch of
+// its own.  Which batches take it: make_plan.
+constexpr int kRowsWaves = 16;
+constexpr int kRowsThreads = kRowsWaves * kWave;
+constexpr size_t kRowsLds = 160 * 1024;
+
+struct RowsChunk {
+  unsigned long long word;   // candidates among 64 window positions
+  int first;                 // slot of the first of them
+  int before;                // candidates of all chunks before
+  int len;                   // positions
+};
+
+// 64-position chunks of a sequence's window at most
+__host__ __device__ inline int rows_chunks(int L) { return ((L < kMaxBlock ? L : kMaxBlock) + kWave - 1) / kWave; }
+template <class Vec, int U>
+constexpr size_t rows_kept_bytes() { return (size_t)U * (kRowsWaves + 1) * kWave * sizeof(typename Vec::Raw); }
+
+// Every chunk's candidates and their running counts, by the whole workgroup;
+// returns the number of candidates.  Three round trips to memory and LDS in
+// all, whatever B: the bounds, the mask bytes (kRowsBatch chunks a wave in
+// flight), the counts.
+__device__ __forceinline__ int rows_find(RowsChunk* chunk, int* s_wave, int B, int L,
+                                         const uint8_t* __restrict__ mask,
+                                         const int32_t* __restrict__ bstart,
+                                         const int32_t* __restrict__ bend) {
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int C = rows_chunks(L), nc = B * C;
+  for (int k = tid; k < nc; k += kRowsThreads) {
+    const int b = (int)((unsigned)k / (unsigned)C), c = k - b * C;
+    const int s = bstart[b], e = bend[b];
+    const int n = window_ok(s, e, L) ? max(0, min(e - s - c * kWave, kWave)) : 0;
+    chunk[k].len = n;
+    chunk[k].first = n > 0 ? b * L + s + c * kWave : 0;
+  }
+  __syncthreads();
+  constexpr int kRowsBatch = 16;
+  for (int k0 = wave; k0 < nc; k0 += kRowsWaves * kRowsBatch) {
+    uint8_t m[kRowsBatch];
+#pragma unroll
+    for (int i = 0; i < kRowsBatch; ++i) {
+      const int k = k0 + i * kRowsWaves;
+      const bool in = k < nc && lane < chunk[k < nc ? k : 0].len;
+      m[i] = mask[in ? chunk[k < nc ? k : 0].first + lane : 0];     // past the chunk: slot 0, not used
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kRowsBatch; ++i) {
+      const int k = k0 + i * kRowsWaves;
+      if (k >= nc) break;
+      const unsigned long long w = __ballot(lane < chunk[k].len && m[i] != 0);
+      if (lane == 0) chunk[k].word = w;
+    }
+  }
+  __syncthreads();
+  // running counts: thread t takes the chunks [t per, (t + 1) per)
+  const int per = (nc + kRowsThreads - 1) / kRowsThreads;
+  int own = 0;
+  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) own += __popcll(chunk[k].word);
+  int incl = own;
+#pragma unroll
+  for (int x = 1; x < kWave; x <<= 1) {
+    const int o = __shfl_up(incl, x);
+    if (lane >= x) incl += o;
+  }
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int run = incl - own, total = 0;
+#pragma unroll
+  for (int w = 0; w < kRowsWaves; ++w) {
+    if (w < wave) run += s_wave[w];
+    total += s_wave[w];
+  }
+  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) {
+    chunk[k].before = run;
+    run += __popcll(chunk[k].word);
+  }
+  __syncthreads();
+  return total;
+}
+
+// The default outputs of the non-candidates, shared by all workgroups.
+__device__ __forceinline__ void rows_defaults(const RowsChunk* chunk, int B, int L, const RowOut& out) {
+  const int C = rows_chunks(L), slots = B * L;
+  for (int p = blockIdx.x * kRowsThreads + (int)threadIdx.x; p < slots; p += gridDim.x * kRowsThreads) {
+    const int b = (int)((unsigned)p / (unsigned)L);
+    const int first = chunk[b * C].first;      // of the window; an empty one has no candidates
+    const int rel = p - first;
+    const bool in = rel >= 0 && rel < C * kWave && first >= b * L;
+    const unsigned long long word = in ? chunk[b * C + rel / kWave].word : 0ull;
+    if (((word >> (rel % kWave)) & 1ull) == 0ull) store_default(out, (size_t)p);
+  }
+}
+
+// The last chunk of [0, nc) with before <= r.
+__device__ __forceinline__ int rows_search(const RowsChunk* chunk, int nc, int r) {
+  int lo = 0, hi = nc - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (chunk[mid].before <= r) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Streams the rows [r0, r1) of a workgroup: wave w starts with row r0 + w, so
+// the waves of a CU stream neighbouring rows (rows a power of two apart share
+// memory channels) and few rows spread over its SIMDs; then each takes the
+// next.  `done(k, r, slot, result)` per row, k its chunk.
+template <class Vec, int U, class F>
+__device__ __forceinline__ void rows_stream(const typename Vec::Raw* __restrict__ logits, int nvec,
+                                            const RowsChunk* chunk, int nc, int r0, int r1, int* s_next,
+                                            typename Vec::Raw* s_kept, F&& done) {
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  int r = r0 + wave;
+  if (r >= r1) return;
+  int k = rows_search(chunk, nc, r);
+  for (;;) {
+    while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
+    k = __builtin_amdgcn_readfirstlane(k);
+    // the (r - before)-th candidate of the chunk
+    const unsigned long long word = chunk[k].word;
+    const int rank = __popcll(word & ((1ull << lane) - 1ull));
+    const int pos = (int)__builtin_ctzll(__ballot(((word >> lane) & 1ull) && rank == r - chunk[k].before));
+    const int slot = __builtin_amdgcn_readfirstlane(chunk[k].first + pos);
+    const WavePartial wp = row_pass<Vec, U, 1>(logits + (size_t)slot * nvec, nvec, 0,
+                                               s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
+    done(k, r, slot, finish_row_x(wp.m, wp.K, wp.S, wp.first));
+    int next = 0;
+    if (lane == 0) next = atomicAdd(s_next, 1);
+    r = r0 + kRowsWaves + __builtin_amdgcn_readfirstlane(next);
+    if (r >= r1) return;
+  }
+}
+
+template <class Vec, int U>
+__global__ void __launch_bounds__(kRowsThreads)
+k_rows(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+       const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
+       const int32_t* __restrict__ bend, RowOut out) {
+  extern __shared__ __attribute__((aligned(16))) char rows_lds[];
+  typename Vec::Raw* s_kept = reinterpret_cast<typename Vec::Raw*>(rows_lds);
+  RowsChunk* chunk = reinterpret_cast<RowsChunk*>(rows_lds + rows_kept_bytes<Vec, U>());
+  __shared__ int s_wave[kRowsWaves];
+  __shared__ int s_next;
+  if (threadIdx.x == 0) s_next = 0;
+  const int total = rows_find(chunk, s_wave, B, L, mask, bstart, bend);
+  rows_defaults(chunk, B, L, out);
+  const int r0 = __builtin_amdgcn_readfirstlane((int)((long long)blockIdx.x * total / gridDim.x));
+  const int r1 = __builtin_amdgcn_readfirstlane((int)((long long)(blockIdx.x + 1) * total / gridDim.x));
+  rows_stream<Vec, U>(logits, nvec, chunk, B * rows_chunks(L), r0, r1, &s_next, s_kept,
+                      [&](int, int, int slot, const RowResult& rr) {
+                        if (threadIdx.x % kWave == 0) store_row(out, (size_t)slot, rr);
+                      });
+}
+
 __global__ void __launch_bounds__(256) k_reveal(const uint8_t* __restrict__ commit,
                                                  const int32_t* __restrict__ tokens,
                                                  int32_t* __restrict__ x, uint8_t* __restrict__ mask,
@@ -1135,6 +1317,7 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Raw* __restri
 // ---------------------------------------------------------------------------
 struct Plan {
   bool fused;   // one workgroup per sequence, selection in the same kernel
+  bool rows;    // or, where the outputs have a place: evenly shared rows, then the selection
   int split;    // wavefronts per row in the confidence kernel
   int parts;    // decode step with a workspace: split over split / 4 workgroups (0: no)
   int rem;      // fused: the last rem sequences take the small-batch plan, beside (0: none)
@@ -1158,6 +1341,7 @@ static int device_cus() {
 }
 
 constexpr int kFusedMinB = FDLLM_FUSED_MIN_B;
+constexpr int kRowsMaxB = FDLLM_ROWS_MAX_B;           // batches below take the evenly shared rows
 constexpr int kHybridMaxRem = FDLLM_HYBRID_MAX_REM;   // largest remainder run beside the main kernel
 constexpr int kFusedWaves = FDLLM_FUSED_WAVES;   // waves per workgroup in the fused kernel
 constexpr int kTargetWaves = FDLLM_TARGET_WAVES;   // row-streaming waves the split aims for
@@ -1170,7 +1354,17 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
   const long long win = L <= kWaveBlock ? L : row_groups(B, L);
   p.fused = B >= kFusedMinB;
   p.split = 1;
-  if (p.fused) {
+  // From 256 sequences the rows are not split (a row's sums are in one order
+  // in every kernel that can take it, so the plan can follow from what the
+  // caller gives).  Below 768, up to three sequences per CU, they are shared
+  // evenly (k_rows): at V = 126464, blocks of 32 with 1..32 masked, 256
+  // sequences 275 -> 198 us, 512 494 -> 364, 700 706 -> 491; 300 sequences,
+  // blocks of 128 with 32..128 masked, V = 32000 338 -> 281; blocks with all
+  // positions masked, where k_fused has no imbalance, lose the selection's
+  // launch: 328 -> 334, 647 -> 653.  At 1024 sequences that launch and the
+  // search cost every full block 17 of 1229 us, so k_fused keeps it.
+  p.rows = p.fused && B < kRowsMaxB;
+  if (p.fused && !p.rows) {
     // one 8-wave workgroup per sequence fills a CU, so a few sequences beyond
     // a multiple of the CU count would make a second round that leaves most
     // CUs idle; they take the small-batch plan instead, on a side stream
@@ -1310,6 +1504,56 @@ hipError_t launch_select(fdllm_selector sel, const SelectIO& io, int B, int L, f
   return launch_select(sel, io, B, L, param, st, 0, nullptr, RowOut{});
 }
 
+// The kernels over evenly shared rows: whether their LDS holds the batch, and
+// the launches (one workgroup per CU, all resident).
+static constexpr size_t kRowsLdsMax = kRowsLds - 512;   // less the kernels' static part
+
+template <class Vec>
+static bool rows_fit(int B, int L) {
+  const long long nc = (long long)B * rows_chunks(L);
+  return (long long)B * L <= 0x7fffffffLL &&
+         nc * (long long)sizeof(RowsChunk) + (long long)rows_kept_bytes<Vec, Vec::kU>() <= (long long)kRowsLdsMax;
+}
+
+// The LDS limit is raised once per device, before the first launch there.
+template <class Vec>
+static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, const uint8_t* mask,
+                                const int32_t* bs, const int32_t* be, RowOut out, hipStream_t st) {
+  static std::atomic<bool> allowed[64];
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!allowed[dev].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute((const void*)k_rows<Vec, Vec::kU>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowsLdsMax);
+    if (e != hipSuccess) return e;
+    allowed[dev].store(true, std::memory_order_release);
+  }
+  const size_t lds = rows_kept_bytes<Vec, Vec::kU>() + (size_t)B * rows_chunks(L) * sizeof(RowsChunk);
+  hipLaunchKernelGGL((k_rows<Vec, Vec::kU>), dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
+                     (const typename Vec::Raw*)logits, B, L, nvec, mask, bs, be, out);
+  return hipGetLastError();
+}
+
+// The vocabulary pass of a rows plan (Plan::rows): whether it can run here,
+// and the launch.
+static bool rows_ok(const void* logits, fdllm_dtype dt, int B, int L, int V) {
+  if (device_cus() < 1) return false;
+  if (vec_path(logits, V, dt)) return dt == FDLLM_BF16 ? rows_fit<VecBf16x8>(B, L) : rows_fit<VecF32x4>(B, L);
+  return dt == FDLLM_BF16 ? rows_fit<VecBf16x1>(B, L) : rows_fit<VecF32x1>(B, L);
+}
+static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V,
+                              const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
+                              hipStream_t st) {
+  if (vec_path(logits, V, dt)) {
+    if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, mask, bs, be, out, st);
+    return launch_rows_t<VecF32x4>(logits, B, L, V / 4, mask, bs, be, out, st);
+  }
+  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x1>(logits, B, L, V, mask, bs, be, out, st);
+  return launch_rows_t<VecF32x1>(logits, B, L, V, mask, bs, be, out, st);
+}
+
 template <class Vec, int R, bool Robust>
 static void launch_fused_t(const void* logits, int B, int L, int nvec, uint8_t* mask,
                            const int32_t* bs, const int32_t* be, int32_t* x, float param,
@@ -1403,6 +1647,10 @@ static bool sizes_ok(int B, int L, int V) {
 // wave partials of the parts plan
 static size_t out_bytes_for(int B, int L) { return 3 * align256((size_t)B * (size_t)L * 4); }
 static size_t workspace_bytes_for(int B, int L, const Plan& p) {
+  // evenly shared rows: the outputs that the caller does not take (without a
+  // place for them, one workgroup per sequence); none where no device tells
+  // how many workgroups there would be
+  if (p.rows) return device_cus() > 0 ? out_bytes_for(B, L) : 0;
   if (p.fused) {
     if (!p.rem) return 0;
     const size_t n = (size_t)p.rem * (size_t)L;
@@ -1536,6 +1784,10 @@ fdllm_status fdllm_confidence(const void* logits, fdllm_dtype dtype, int B, int 
   const Plan p = make_plan(B, L, V, dtype);
   RowOut out{tokens, conf, eps, lse};
   hipStream_t st = (hipStream_t)stream;
+  if (p.rows && rows_ok(logits, dtype, B, L, V))
+    return launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, out, st) == hipSuccess
+               ? FDLLM_OK
+               : FDLLM_ERR_HIP;
   // the rows of a fused step's small-batch remainder are split as the decode
   // step splits them, so that both give the same bits
   const int b0 = B - p.rem;
@@ -1625,6 +1877,8 @@ fdllm_status fdllm_decode_step(const void* logits, fdllm_dtype dtype, int B, int
 
 namespace fdllm {
 
+bool workspace_optional(int B) { return B >= kFusedMinB && B < kRowsMaxB; }
+
 fdllm_status decode_step(const void* logits, fdllm_dtype dtype, int B, int L, int V, uint8_t* mask,
                          const int32_t* block_start, const int32_t* block_end, int32_t* x,
                          fdllm_selector sel, float param, const float* eta, float eta_uniform,
@@ -1646,10 +1900,21 @@ fdllm_status decode_step(const void* logits, fdllm_dtype dtype, int B, int L, in
   if (!p.fused)
     return step_split(p, sel, logits, dtype, B, L, V, mask, block_start, block_end, x, param, etain,
                       tokens, conf, eps, lse, commit, n_commit, workspace, workspace_bytes, st);
+  const bool outs_given = tokens && conf && eps;
+  if (p.rows && rows_ok(logits, dtype, B, L, V) &&
+      (outs_given || (workspace && workspace_bytes >= out_bytes_for(B, L)))) {
+    const size_t n = align256((size_t)B * (size_t)L * 4);
+    char* ws = (char*)workspace;
+    const RowOut o{tokens ? tokens : (int32_t*)ws, conf ? conf : (float*)(ws + n),
+                   eps ? eps : (float*)(ws + 2 * n), lse};
+    if (launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, o, st) != hipSuccess)
+      return FDLLM_ERR_HIP;
+    const SelectIO io{o.conf, o.eps, mask, block_start, block_end, commit, n_commit, o.tokens, x, etain};
+    return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
+  }
   RowOut out{tokens, conf, eps, lse};
   const int b0 = B - p.rem;
   const Plan q = remainder_plan(p);
-  const bool outs_given = tokens && conf && eps;
   const bool rem_ok = p.rem && (outs_given || (workspace && workspace_bytes >= workspace_bytes_for(B, L, p)));
   const size_t r0 = (size_t)b0 * (size_t)L;
   const size_t esize = dtype == FDLLM_BF16 ? 2 : 4;

@@ -489,3 +489,47 @@ def test_very_confident_rows_eps(gpu, B, L, V, dt):
     for k, t in zip(("tokens", "conf", "eps", "lse"), gc):
         assert np.array_equal(d[k].cpu().numpy().view(np.int32), t.view(np.int32)), k
     say(f"  worst {worst}")
+
+
+@pytest.mark.parametrize("B,L,V,dt,window", [(256, 1, 512, torch.bfloat16, 1), (256, 64, 300, torch.bfloat16, 64),
+                                              (300, 65, 512, torch.float32, 65), (511, 130, 64, torch.bfloat16, 130),
+                                              (767, 8, 1001, torch.bfloat16, 8), (768, 8, 1001, torch.bfloat16, 8),
+                                              (400, 300, 33, torch.float32, 300), (256, 1024, 16, torch.bfloat16, 1024),
+                                              (260, 33, 126464, torch.bfloat16, 33)])
+@pytest.mark.parametrize("p_mask", [0.0, 0.1, 1.0])
+def test_shared_rows_equal_fused_bits(gpu, B, L, V, dt, window, p_mask):
+    """Evenly shared rows (outputs given) and one workgroup per sequence (no
+    place for them) decide the same; the outputs are fdllm_confidence's bits;
+    empty, invalid and whole-span windows; no, few and all positions masked."""
+    inp = workloads.random_case(B, L, V, dt, device="cuda", seed=B + L + V, window=window, p_mask=p_mask, poison=False)
+    start, end = inp.start.clone(), inp.end.clone()
+    start[1], end[1] = -1, 2                       # invalid
+    start[2], end[2] = 0, L                        # the whole span
+    start[3], end[3] = L, L                        # empty, at the end
+    start[4], end[4] = 0, L + 1                    # invalid
+    inp.start, inp.end = start, end
+    say(f"[shared rows] {inp.name} p_mask={p_mask}")
+    ref = gpu_confidence(gpu, inp)
+    got = []
+    for outs in (True, False):
+        mask, x = inp.mask.clone(), inp.x.clone()
+        o = {"commit": torch.full((B, L), 9, dtype=torch.uint8, device="cuda"),
+             "n_commit": torch.full((B,), -9, dtype=torch.int32, device="cuda")}
+        if outs:
+            o["tokens"] = torch.full((B, L), -7, dtype=torch.int32, device="cuda")
+            for k in ("conf", "eps", "lse"):
+                o[k] = torch.full((B, L), -7.0, device="cuda")
+        gpu.fdllm_decode_step(inp.logits, mask, start, end, x, "profile", 1.0,
+                              workspace=torch.empty(1, dtype=torch.uint8, device="cuda"), **o)
+        torch.cuda.synchronize()
+        got.append((mask, x, o["commit"], o["n_commit"]))
+        if outs:
+            for k, t in zip(("tokens", "conf", "eps", "lse"), ref):
+                assert torch.equal(o[k].view(torch.uint8), t.view(torch.uint8)), k
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    check_defaults(*[t.cpu().numpy() for t in ref], inp.mask.cpu().numpy(),
+                   [0 if b in (1, 4) else int(s) for b, s in enumerate(start.tolist())],
+                   [0 if b in (1, 4) else int(e) for b, e in enumerate(end.tolist())], range(B))
+    n = got[0][3].cpu()
+    assert n[1] == -1 and n[4] == -1 and n[3] == 0
