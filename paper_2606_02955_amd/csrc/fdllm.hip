@@ -98,9 +98,18 @@ __host__ __device__ inline int row_groups(int B, int L) {
 }
 
 // ---------------------------------------------------------------------------
-// vector formats: one lane loads 16 bytes (or one element on the scalar path)
+// vector formats: one lane loads 16 bytes
 // ---------------------------------------------------------------------------
+// Rows whose length or start is no multiple of 16 bytes (kAny) are cut into
+// the same row-relative vectors, loaded from where they lie (global loads need
+// no more than the element's alignment), and a last one of the remaining
+// elements, each loaded by itself and padded; so an element belongs to the
+// same lane, and a row has the same bits, wherever it starts.  Loading such
+// rows element by element took 327 us for 1024 full blocks of 16 rows at
+// V = 50257 (bf16), these loads 282; 256 blocks of 32 at V = 126465 474 and 366.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 
 // bit pattern of FDLLM_MAX_ABS_LOGIT as a float; for finite and non-finite
 // values alike, |x| > bound  <=>  (bits(x) & 0x7FFFFFFF) > kBoundBits
@@ -112,7 +121,11 @@ struct VecBf16x8 {
   static constexpr int kElems = 8;
   static constexpr int kU = FDLLM_U_BF16;   // vectors per lane per batch
   static constexpr int kUSplit = FDLLM_U_SPLIT_BF16;   // the same, rows split over waves
+  static constexpr bool kAny = false;
   using Raw = u32x4;
+  using Mem = u32x4;                        // as it lies in memory
+  using Elem = unsigned short;
+  __device__ static unsigned f32_bits(Elem e) { return (unsigned)e << 16; }
   __device__ static Raw pad() { return Raw{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u}; }
   __device__ static void unpack(const Raw& r, float (&x)[kElems]) {
     x[0] = __uint_as_float(r.x << 16); x[1] = __uint_as_float(r.x & 0xFFFF0000u);
@@ -130,7 +143,11 @@ struct VecF32x4 {
   static constexpr int kElems = 4;
   static constexpr int kU = FDLLM_U_F32;
   static constexpr int kUSplit = FDLLM_U_F32;
+  static constexpr bool kAny = false;
   using Raw = u32x4;
+  using Mem = u32x4;
+  using Elem = unsigned int;
+  __device__ static unsigned f32_bits(Elem e) { return e; }
   __device__ static Raw pad() { return Raw{0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u}; }
   __device__ static void unpack(const Raw& r, float (&x)[kElems]) {
     x[0] = __uint_as_float(r.x); x[1] = __uint_as_float(r.y);
@@ -140,27 +157,41 @@ struct VecF32x4 {
     return bad_bits(r.x) | bad_bits(r.y) | bad_bits(r.z) | bad_bits(r.w);
   }
 };
-struct VecBf16x1 {
-  static constexpr int kElems = 1;
-  static constexpr int kU = 8;
-  static constexpr int kUSplit = 8;
-  using Raw = unsigned short;
-  __device__ static Raw pad() { return (unsigned short)0xFF80u; }
-  __device__ static void unpack(const Raw& r, float (&x)[kElems]) { x[0] = __uint_as_float((unsigned)r << 16); }
-  __device__ static bool bad(const Raw& r) { return bad_bits((unsigned)r << 16); }
+struct VecBf16Any : VecBf16x8 {
+  static constexpr bool kAny = true;
+  using Mem = u32x4_a2;
+  __device__ static Raw tail(const Elem* e, int n) {       // n < kElems elements, padded
+    Raw r = pad();
+#pragma unroll
+    for (int i = 0; i < kElems; ++i)
+      if (i < n) r[i / 2] = i % 2 ? (r[i / 2] & 0xFFFFu) | ((unsigned)e[i] << 16) : (r[i / 2] & 0xFFFF0000u) | e[i];
+    return r;
+  }
 };
-struct VecF32x1 {
-  static constexpr int kElems = 1;
-  static constexpr int kU = 8;
-  static constexpr int kUSplit = 8;
-  using Raw = unsigned int;
-  __device__ static Raw pad() { return 0xFF800000u; }
-  __device__ static void unpack(const Raw& r, float (&x)[kElems]) { x[0] = __uint_as_float(r); }
-  __device__ static bool bad(const Raw& r) { return bad_bits(r); }
+struct VecF32Any : VecF32x4 {
+  static constexpr bool kAny = true;
+  using Mem = u32x4_a4;
+  __device__ static Raw tail(const Elem* e, int n) {
+    Raw r = pad();
+#pragma unroll
+    for (int i = 0; i < kElems; ++i)
+      if (i < n) r[i] = e[i];
+    return r;
+  }
 };
 
-template <class Raw>
-__device__ __forceinline__ Raw load_stream(const Raw* p) {
+// Row `slot` of the logits; n: a row's vectors, or its elements where kAny.
+template <class Vec>
+__device__ __forceinline__ const typename Vec::Mem* row_at(const typename Vec::Mem* logits, size_t slot, int n) {
+  if constexpr (Vec::kAny)
+    return reinterpret_cast<const typename Vec::Mem*>(reinterpret_cast<const typename Vec::Elem*>(logits) +
+                                                      slot * (size_t)n);
+  else
+    return logits + slot * (size_t)n;
+}
+
+template <class Mem>
+__device__ __forceinline__ u32x4 load_stream(const Mem* p) {
   return __builtin_nontemporal_load(p);
 }
 
@@ -173,16 +204,18 @@ constexpr int kAcc = 4;   // independent double accumulators per lane
 // The wave handles wave-loads k = w, w+S, w+2S, ... of the row (a wave-load
 // is 64 consecutive vectors); lane l reads vector k*64 + l.
 template <class Vec, int U, int S>
-__device__ __forceinline__ WavePartial row_pass(const typename Vec::Raw* __restrict__ row, int nvec, int w,
+__device__ __forceinline__ WavePartial row_pass(const typename Vec::Mem* __restrict__ row, int n, int w,
                                                 typename Vec::Raw* kept, typename Vec::Raw* unkept) {
   using Raw = typename Vec::Raw;
   constexpr int E = Vec::kElems;
   const int lane = lane_id();
+  // vectors of the row, and those that are whole
+  const int nvec = Vec::kAny ? (n + E - 1) / E : n, nwhole = Vec::kAny ? n / E : n;
   const int nwl = (nvec + kWave - 1) / kWave;          // wave-loads in the row
-  const int nfull = nvec / kWave;                       // wave-loads with no padding
+  const int nfull = nwhole / kWave;                     // wave-loads with no padding
   const int nj = nwl > w ? (nwl - w + S - 1) / S : 0;   // this wave's wave-loads
   const int njf = nfull > w ? (nfull - w + S - 1) / S : 0;
-  const Raw* p = row + w * kWave + lane;
+  const typename Vec::Mem* p = row + w * kWave + lane;
   constexpr int kStride = S * kWave;
 
   float m = kNegInf;
@@ -256,7 +289,11 @@ __device__ __forceinline__ WavePartial row_pass(const typename Vec::Raw* __restr
     for (int u = 0; u < U; ++u) {
       const int j = jb * U + u;
       const int v = (w + j * S) * kWave + lane;
-      r[u] = (j < nj && v < nvec) ? load_stream(p + j * kStride) : Vec::pad();
+      r[u] = (j < nj && v < nwhole) ? load_stream(p + j * kStride) : Vec::pad();
+      if constexpr (Vec::kAny) {
+        if (j < nj && v == nwhole && v < nvec)
+          r[u] = Vec::tail(reinterpret_cast<const typename Vec::Elem*>(row) + (size_t)v * E, n - v * E);
+      }
     }
   };
   Raw ra[U], rb[U];
@@ -426,7 +463,7 @@ __device__ __forceinline__ RowResult combine_parts(const WavePartial* part) {
 // only B W row groups are launched, however long the span L.
 template <class Vec, int U, int S>
 __global__ void __launch_bounds__(SplitShape<S>::kThreads)
-k_confidence(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
              const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
              const int32_t* __restrict__ bend, RowOut out) {
   using Shape = SplitShape<S>;
@@ -467,7 +504,7 @@ k_confidence(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
     const bool cand = inwin && mask[slot] != 0;
     WavePartial wp{};
     if (cand)
-      wp = row_pass<Vec, U, S>(logits + (long long)slot * nvec, nvec, w, s_kept + wave * U * kWave,
+      wp = row_pass<Vec, U, S>(row_at<Vec>(logits, slot, nvec), nvec, w, s_kept + wave * U * kWave,
                                s_kept + Shape::kWaves * U * kWave);
     if constexpr (S > 1) {
       if (lane == 0) part[wave] = wp;
@@ -496,7 +533,7 @@ k_confidence(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
 // defaults here.
 template <class Vec, int U, int S>
 __global__ void __launch_bounds__(256)
-k_confidence_parts(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+k_confidence_parts(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
                    const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
                    const int32_t* __restrict__ bend, RowOut out, WavePartial* __restrict__ parts) {
   constexpr int P = S / 4;                                  // workgroups per slot
@@ -514,7 +551,7 @@ k_confidence_parts(const typename Vec::Raw* __restrict__ logits, int B, int L, i
     if (w == 0 && lane == 0) store_default(out, (size_t)slot);
     return;
   }
-  const WavePartial wp = row_pass<Vec, U, S>(logits + slot * (long long)nvec, nvec, w, s_kept + wave * U * kWave,
+  const WavePartial wp = row_pass<Vec, U, S>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, w, s_kept + wave * U * kWave,
                                              s_kept + U * 256);
   if (lane == 0) parts[slot * S + w] = wp;
 }
@@ -924,7 +961,7 @@ __global__ void __launch_bounds__(W * kWave)
 #if FDLLM_WAVES_PER_EU > 0
 __attribute__((amdgpu_waves_per_eu(FDLLM_WAVES_PER_EU)))
 #endif
-k_fused(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+k_fused(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
         uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
         const int32_t* __restrict__ bend, int32_t* __restrict__ x, float param, EtaIn eta,
         RowOut out, uint8_t* __restrict__ commit, int32_t* __restrict__ n_commit) {
@@ -962,7 +999,7 @@ k_fused(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
     const int slot = s_cand[c];
     const size_t r = row0 + s + slot;
     typename Vec::Raw* kept = s_kept + wave * 2 * U * kWave;
-    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, kept, kept + U * kWave);
+    const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, r, nvec), nvec, 0, kept, kept + U * kWave);
     const RowResult rr = finish_row_x(wp.m, wp.K, wp.S, wp.first);
     if (lane == 0) {
       store_row(out, r, rr);
@@ -995,7 +1032,7 @@ k_fused(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
 // k_select_wide.
 template <class Vec, int U, int W, int R, bool Robust>
 __global__ void __launch_bounds__(W * kWave)
-k_fused_wide(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+k_fused_wide(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
              uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
              const int32_t* __restrict__ bend, int32_t* __restrict__ x, float param, EtaIn eta,
              RowOut out, uint8_t* __restrict__ commit, int32_t* __restrict__ n_commit) {
@@ -1035,7 +1072,7 @@ k_fused_wide(const typename Vec::Raw* __restrict__ logits, int B, int L, int nve
     const int slot = s_cand[c];
     const size_t r = row0 + s + slot;
     typename Vec::Raw* kept = s_kept + wave * 2 * U * kWave;
-    const WavePartial wp = row_pass<Vec, U, 1>(logits + r * (size_t)nvec, nvec, 0, kept, kept + U * kWave);
+    const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, r, nvec), nvec, 0, kept, kept + U * kWave);
     const RowResult rr = finish_row_x(wp.m, wp.K, wp.S, wp.first);
     if (lane == 0) {
       store_row(out, r, rr);
@@ -1217,7 +1254,7 @@ __device__ __forceinline__ int rows_search(const RowsChunk* chunk, int nc, int r
 // memory channels) and few rows spread over its SIMDs; then each takes the
 // next.  `done(k, r, slot, result)` per row, k its chunk.
 template <class Vec, int U, class F>
-__device__ __forceinline__ void rows_stream(const typename Vec::Raw* __restrict__ logits, int nvec,
+__device__ __forceinline__ void rows_stream(const typename Vec::Mem* __restrict__ logits, int nvec,
                                             const RowsChunk* chunk, int nc, int r0, int r1, int* s_next,
                                             typename Vec::Raw* s_kept, F&& done) {
   const int lane = threadIdx.x % kWave;
@@ -1233,7 +1270,7 @@ __device__ __forceinline__ void rows_stream(const typename Vec::Raw* __restrict_
     const int rank = __popcll(word & ((1ull << lane) - 1ull));
     const int pos = (int)__builtin_ctzll(__ballot(((word >> lane) & 1ull) && rank == r - chunk[k].before));
     const int slot = __builtin_amdgcn_readfirstlane(chunk[k].first + pos);
-    const WavePartial wp = row_pass<Vec, U, 1>(logits + (size_t)slot * nvec, nvec, 0,
+    const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, 0,
                                                s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
     done(k, r, slot, finish_row_x(wp.m, wp.K, wp.S, wp.first));
     int next = 0;
@@ -1245,7 +1282,7 @@ __device__ __forceinline__ void rows_stream(const typename Vec::Raw* __restrict_
 
 template <class Vec, int U>
 __global__ void __launch_bounds__(kRowsThreads)
-k_rows(const typename Vec::Raw* __restrict__ logits, int B, int L, int nvec,
+k_rows(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
        const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
        const int32_t* __restrict__ bend, RowOut out) {
   extern __shared__ __attribute__((aligned(16))) char rows_lds[];
@@ -1287,7 +1324,7 @@ __global__ void k_check_clear(int32_t* __restrict__ counts) {
 }
 
 template <class Vec>
-__global__ void __launch_bounds__(256) k_check(const typename Vec::Raw* __restrict__ logits, int B,
+__global__ void __launch_bounds__(256) k_check(const typename Vec::Mem* __restrict__ logits, int B,
                                                int L, int nvec, const uint8_t* __restrict__ mask,
                                                const int32_t* __restrict__ bstart,
                                                const int32_t* __restrict__ bend,
@@ -1306,9 +1343,14 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Raw* __restri
     return;
   }
   if (i < s || i >= e || mask[slot] == 0) return;
-  const typename Vec::Raw* row = logits + slot * (long long)nvec;
+  const typename Vec::Mem* row = row_at<Vec>(logits, (size_t)slot, nvec);
   bool bad = false;
-  for (int v = lane; v < nvec; v += kWave) bad |= Vec::bad(load_stream(row + v));
+  const int nwhole = Vec::kAny ? nvec / Vec::kElems : nvec;
+  for (int v = lane; v < nwhole; v += kWave) bad |= Vec::bad(load_stream(row + v));
+  if constexpr (Vec::kAny) {
+    const int i = nwhole * Vec::kElems + lane;
+    if (i < nvec) bad |= bad_bits(Vec::f32_bits(reinterpret_cast<const typename Vec::Elem*>(row)[i]));
+  }
   if (__ballot(bad) != 0ull && lane == 0) atomicAdd(&counts[2], 1);
 }
 
@@ -1400,7 +1442,7 @@ static hipError_t launch_confidence_t(const void* logits, int B, int L, int nvec
                                       const uint8_t* mask, const int32_t* bs, const int32_t* be,
                                       RowOut out, hipStream_t st) {
   const long long nvslots = (long long)B * row_groups(B, L);   // window-relative
-  const auto* lg = (const typename Vec::Raw*)logits;
+  const auto* lg = (const typename Vec::Mem*)logits;
 #define FDLLM_CONF_CASE(SPLIT)                                                                  \
   case SPLIT: {                                                                                 \
     using Sh = SplitShape<SPLIT>;                                                               \
@@ -1429,7 +1471,7 @@ static hipError_t launch_confidence_parts_t(const void* logits, int B, int L, in
                                             const int32_t* be, RowOut out, WavePartial* parts,
                                             hipStream_t st) {
   const long long nslots = (long long)B * L;
-  const auto* lg = (const typename Vec::Raw*)logits;
+  const auto* lg = (const typename Vec::Mem*)logits;
   const dim3 grid((unsigned)(nslots * (split / 4))), block(256);
   if (split == 8)
     hipLaunchKernelGGL((k_confidence_parts<Vec, Vec::kUSplit, 8>), grid, block, 0, st, lg, B, L, nvec,
@@ -1454,8 +1496,8 @@ static hipError_t launch_confidence_parts(const void* logits, fdllm_dtype dt, in
                                                st);
   }
   if (dt == FDLLM_BF16)
-    return launch_confidence_parts_t<VecBf16x1>(logits, B, L, V, split, mask, bs, be, out, parts, st);
-  return launch_confidence_parts_t<VecF32x1>(logits, B, L, V, split, mask, bs, be, out, parts, st);
+    return launch_confidence_parts_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, parts, st);
+  return launch_confidence_parts_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, parts, st);
 }
 
 static hipError_t launch_confidence(const void* logits, fdllm_dtype dt, int B, int L, int V,
@@ -1467,8 +1509,8 @@ static hipError_t launch_confidence(const void* logits, fdllm_dtype dt, int B, i
     return launch_confidence_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, st);
   }
   if (dt == FDLLM_BF16)
-    return launch_confidence_t<VecBf16x1>(logits, B, L, V, split, mask, bs, be, out, st);
-  return launch_confidence_t<VecF32x1>(logits, B, L, V, split, mask, bs, be, out, st);
+    return launch_confidence_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, st);
+  return launch_confidence_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, st);
 }
 
 template <int R, bool Robust>
@@ -1532,7 +1574,7 @@ static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, cons
   }
   const size_t lds = rows_kept_bytes<Vec, Vec::kU>() + (size_t)B * rows_chunks(L) * sizeof(RowsChunk);
   hipLaunchKernelGGL((k_rows<Vec, Vec::kU>), dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
-                     (const typename Vec::Raw*)logits, B, L, nvec, mask, bs, be, out);
+                     (const typename Vec::Mem*)logits, B, L, nvec, mask, bs, be, out);
   return hipGetLastError();
 }
 
@@ -1541,7 +1583,7 @@ static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, cons
 static bool rows_ok(const void* logits, fdllm_dtype dt, int B, int L, int V) {
   if (device_cus() < 1) return false;
   if (vec_path(logits, V, dt)) return dt == FDLLM_BF16 ? rows_fit<VecBf16x8>(B, L) : rows_fit<VecF32x4>(B, L);
-  return dt == FDLLM_BF16 ? rows_fit<VecBf16x1>(B, L) : rows_fit<VecF32x1>(B, L);
+  return dt == FDLLM_BF16 ? rows_fit<VecBf16Any>(B, L) : rows_fit<VecF32Any>(B, L);
 }
 static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V,
                               const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
@@ -1550,8 +1592,8 @@ static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, 
     if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, mask, bs, be, out, st);
     return launch_rows_t<VecF32x4>(logits, B, L, V / 4, mask, bs, be, out, st);
   }
-  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x1>(logits, B, L, V, mask, bs, be, out, st);
-  return launch_rows_t<VecF32x1>(logits, B, L, V, mask, bs, be, out, st);
+  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16Any>(logits, B, L, V, mask, bs, be, out, st);
+  return launch_rows_t<VecF32Any>(logits, B, L, V, mask, bs, be, out, st);
 }
 
 template <class Vec, int R, bool Robust>
@@ -1561,11 +1603,11 @@ static void launch_fused_t(const void* logits, int B, int L, int nvec, uint8_t* 
                            hipStream_t st) {
   if (L <= kWaveBlock)
     hipLaunchKernelGGL((k_fused<Vec, Vec::kU, kFusedWaves, R, Robust>), dim3((unsigned)B),
-                       dim3(kFusedWaves * kWave), 0, st, (const typename Vec::Raw*)logits, B, L,
+                       dim3(kFusedWaves * kWave), 0, st, (const typename Vec::Mem*)logits, B, L,
                        nvec, mask, bs, be, x, param, eta, out, commit, n_commit);
   else
     hipLaunchKernelGGL((k_fused_wide<Vec, Vec::kU, kFusedWaves, R, Robust>), dim3((unsigned)B),
-                       dim3(kFusedWaves * kWave), 0, st, (const typename Vec::Raw*)logits, B, L,
+                       dim3(kFusedWaves * kWave), 0, st, (const typename Vec::Mem*)logits, B, L,
                        nvec, mask, bs, be, x, param, eta, out, commit, n_commit);
 }
 
@@ -1607,9 +1649,9 @@ static hipError_t launch_fused(fdllm_selector sel, const void* logits, fdllm_dty
                                     commit, n_commit, st);
   }
   if (dt == FDLLM_BF16)
-    return launch_fused_v<VecBf16x1>(sel, logits, B, L, V, mask, bs, be, x, param, eta, out, commit,
+    return launch_fused_v<VecBf16Any>(sel, logits, B, L, V, mask, bs, be, x, param, eta, out, commit,
                                      n_commit, st);
-  return launch_fused_v<VecF32x1>(sel, logits, B, L, V, mask, bs, be, x, param, eta, out, commit,
+  return launch_fused_v<VecF32Any>(sel, logits, B, L, V, mask, bs, be, x, param, eta, out, commit,
                                   n_commit, st);
 }
 
@@ -1745,11 +1787,11 @@ fdllm_status fdllm_check_inputs(const void* logits, fdllm_dtype dtype, int B, in
         hipLaunchKernelGGL(k_check<VecF32x4>, dim3(grid), dim3(256), 0, st,
                            (const u32x4*)logits, B, L, V / 4, mask, block_start, block_end, counts);
     } else if (dtype == FDLLM_BF16) {
-      hipLaunchKernelGGL(k_check<VecBf16x1>, dim3(grid), dim3(256), 0, st,
-                         (const unsigned short*)logits, B, L, V, mask, block_start, block_end, counts);
+      hipLaunchKernelGGL(k_check<VecBf16Any>, dim3(grid), dim3(256), 0, st,
+                         (const u32x4_a2*)logits, B, L, V, mask, block_start, block_end, counts);
     } else {
-      hipLaunchKernelGGL(k_check<VecF32x1>, dim3(grid), dim3(256), 0, st,
-                         (const unsigned int*)logits, B, L, V, mask, block_start, block_end, counts);
+      hipLaunchKernelGGL(k_check<VecF32Any>, dim3(grid), dim3(256), 0, st,
+                         (const u32x4_a4*)logits, B, L, V, mask, block_start, block_end, counts);
     }
   }
   if (hipGetLastError() != hipSuccess) return FDLLM_ERR_HIP;

@@ -533,3 +533,42 @@ def test_shared_rows_equal_fused_bits(gpu, B, L, V, dt, window, p_mask):
                    [0 if b in (1, 4) else int(e) for b, e in enumerate(end.tolist())], range(B))
     n = got[0][3].cpu()
     assert n[1] == -1 and n[4] == -1 and n[3] == 0
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [1, 3, 7, 8, 9, 63, 64, 65, 511, 513, 2049, 8190, 50257])
+def test_rows_of_any_length_and_start(gpu, V, dt):
+    """Rows whose length or first byte is no multiple of 16 bytes: the oracle's
+    results, and for equal rows equal bits wherever they start (the span's rows
+    start at every element offset, in a view one element into its buffer)."""
+    B, L = 3, 20
+    g = torch.Generator().manual_seed(V)
+    row = (torch.randn(V, generator=g) * 3).to(dt)
+    buf = torch.empty(B * L * V + 1, dtype=dt, device="cuda")
+    logits = buf[1:].view(B, L, V)
+    logits.copy_((torch.randn((B, L, V), generator=g) * 3).to(dt))
+    logits[1] = row.cuda()
+    mask = torch.ones((B, L), dtype=torch.uint8, device="cuda")
+    start = torch.zeros(B, dtype=torch.int32, device="cuda")
+    end = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    say(f"[any rows] V={V} {dt}")
+    out = [torch.full((B, L), -7, dtype=torch.int32, device="cuda")] + \
+          [torch.full((B, L), -7.0, device="cuda") for _ in range(3)]
+    gpu.fdllm_confidence(logits, mask, start, end, *out)
+    aligned = [torch.empty_like(t) for t in out]
+    gpu.fdllm_confidence(logits.clone(), mask, start, end, *aligned)
+    torch.cuda.synchronize()
+    for t, a in zip(out, aligned):
+        assert torch.equal(t, a)
+        assert bool((t[1] == t[1, 0]).all())
+    o = oracle.confidence(row_source(logits), B, L, mask.cpu().numpy(), start.cpu().numpy(), end.cpu().numpy())
+    compare_rows(*[t.cpu().numpy() for t in out], *o, candidates(mask.cpu().numpy(), start.cpu().numpy(),
+                                                               end.cpu().numpy(), range(B)))
+    status, counts = gpu.fdllm_check_inputs(logits, mask, start, end)
+    assert status == gpu.OK and counts == [0, 0, 0]
+    for i in range(V):
+        if i in (0, V // 2, V - 1):
+            bad = logits.clone()
+            bad[2, 5, i] = float("inf")
+            status, counts = gpu.fdllm_check_inputs(bad, mask, start, end)
+            assert status == gpu.ERR_NONFINITE and counts == [0, 0, 1]
