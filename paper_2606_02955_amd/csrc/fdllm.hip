@@ -1249,6 +1249,14 @@ __device__ __forceinline__ int rows_search(const RowsChunk* chunk, int nc, int r
   return lo;
 }
 
+// The slot of row r: the (r - before)-th candidate of its chunk.
+__device__ __forceinline__ int rows_slot(const RowsChunk& c, int r) {
+  const int lane = threadIdx.x % kWave;
+  const int rank = __popcll(c.word & ((1ull << lane) - 1ull));
+  const int pos = (int)__builtin_ctzll(__ballot(((c.word >> lane) & 1ull) && rank == r - c.before));
+  return __builtin_amdgcn_readfirstlane(c.first + pos);
+}
+
 // Streams the rows [r0, r1) of a workgroup: wave w starts with row r0 + w, so
 // the waves of a CU stream neighbouring rows (rows a power of two apart share
 // memory channels) and few rows spread over its SIMDs; then each takes the
@@ -1265,11 +1273,7 @@ __device__ __forceinline__ void rows_stream(const typename Vec::Mem* __restrict_
   for (;;) {
     while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
     k = __builtin_amdgcn_readfirstlane(k);
-    // the (r - before)-th candidate of the chunk
-    const unsigned long long word = chunk[k].word;
-    const int rank = __popcll(word & ((1ull << lane) - 1ull));
-    const int pos = (int)__builtin_ctzll(__ballot(((word >> lane) & 1ull) && rank == r - chunk[k].before));
-    const int slot = __builtin_amdgcn_readfirstlane(chunk[k].first + pos);
+    const int slot = rows_slot(chunk[k], r);
     const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, 0,
                                                s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
     done(k, r, slot, finish_row_x(wp.m, wp.K, wp.S, wp.first));
@@ -1299,6 +1303,68 @@ k_rows(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
                       [&](int, int, int slot, const RowResult& rr) {
                         if (threadIdx.x % kWave == 0) store_row(out, (size_t)slot, rr);
                       });
+}
+
+// The same for rows split over S waves: a workgroup's kRowsWaves / S teams take
+// its rows in turn, every wave its part of a row, and the last wave of a team
+// to finish a row combines the parts, as k_confidence would (the same bits);
+// the others are at the team's next row by then.  A team's parts wait in a
+// ring of kRowsRing rows.
+constexpr int kRowsRing = 8;
+
+template <class Vec, int U, int S>
+__global__ void __launch_bounds__(kRowsThreads)
+k_rows_split(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
+             const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
+             const int32_t* __restrict__ bend, RowOut out) {
+  constexpr int kTeams = kRowsWaves / S;
+  extern __shared__ __attribute__((aligned(16))) char rows_lds[];
+  typename Vec::Raw* s_kept = reinterpret_cast<typename Vec::Raw*>(rows_lds);
+  RowsChunk* chunk = reinterpret_cast<RowsChunk*>(rows_lds + rows_kept_bytes<Vec, U>());
+  __shared__ int s_wave[kRowsWaves];
+  __shared__ WavePartial ring[kRowsRing][kRowsWaves];
+  __shared__ int arrived[kRowsRing][kTeams];    // waves done with the ring's rows
+  __shared__ int combined[kTeams];              // rows a team has combined
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int team = wave / S, w = wave % S;
+  for (int i = threadIdx.x; i < kRowsRing * kTeams; i += kRowsThreads) arrived[i / kTeams][i % kTeams] = 0;
+  if (threadIdx.x < kTeams) combined[threadIdx.x] = 0;
+  const int total = rows_find(chunk, s_wave, B, L, mask, bstart, bend);
+  rows_defaults(chunk, B, L, out);
+  const int nc = B * rows_chunks(L);
+  const int r0 = __builtin_amdgcn_readfirstlane((int)((long long)blockIdx.x * total / gridDim.x));
+  const int r1 = __builtin_amdgcn_readfirstlane((int)((long long)(blockIdx.x + 1) * total / gridDim.x));
+  int r = r0 + team;
+  if (r >= r1) return;
+  int k = rows_search(chunk, nc, r);
+  for (int step = 0; r < r1; r += kTeams, ++step) {
+    while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
+    k = __builtin_amdgcn_readfirstlane(k);
+    const int slot = rows_slot(chunk[k], r);
+    const WavePartial wp = row_pass<Vec, U, S>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, w,
+                                               s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
+    const int at = step % kRowsRing;
+    // the ring's place is free once its row before has been combined; that
+    // waits for no later row, so the wait ends
+    if (step >= kRowsRing)
+      while (__hip_atomic_load(&combined[team], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= step - kRowsRing)
+        __builtin_amdgcn_s_sleep(1);
+    if (lane == 0) ring[at][wave] = wp;
+    __threadfence_block();
+    int before = 0;
+    if (lane == 0) before = atomicAdd(&arrived[at][team], 1);
+    if (__builtin_amdgcn_readfirstlane(before) != S - 1) continue;
+    __threadfence_block();
+    const WavePartial mine = lane < S ? ring[at][team * S + lane]
+                                      : WavePartial{kNegInf, kRefFloor, 0.0, 0x7fffffff};
+    const RowResult rr = combine_parts_lanes<S>(mine);
+    if (lane == 0) {
+      store_row(out, (size_t)slot, rr);
+      arrived[at][team] = 0;
+      __hip_atomic_store(&combined[team], step + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
 }
 
 __global__ void __launch_bounds__(256) k_reveal(const uint8_t* __restrict__ commit,
@@ -1359,7 +1425,8 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Mem* __restri
 // ---------------------------------------------------------------------------
 struct Plan {
   bool fused;   // one workgroup per sequence, selection in the same kernel
-  bool rows;    // or, where the outputs have a place: evenly shared rows, then the selection
+  bool rows;    // where they fit (and, fused, where the outputs have a place): evenly
+                // shared rows, then the selection
   int split;    // wavefronts per row in the confidence kernel
   int parts;    // decode step with a workspace: split over split / 4 workgroups (0: no)
   int rem;      // fused: the last rem sequences take the small-batch plan, beside (0: none)
@@ -1428,6 +1495,18 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
     // a row split 8 or 16 ways fills one CU; blocks of at most one wavefront
     // can take their rows' parts from several workgroups instead
     if (L <= kWaveBlock && p.split >= 8) p.parts = p.split;
+    // A row group is a window position (and those 32 further on), launched
+    // whether or not it is masked: the best grid for blocks of 32, whatever
+    // the span.  A span that is no multiple of 32 holds other blocks, whose
+    // positions beyond 32 take second turns in some row groups; their rows are
+    // shared evenly instead (the search costs about 5 us): at V = 126464 100
+    // full blocks of 48 222 -> 201 us and 24 full blocks of 48 in spans of 96
+    // 86 -> 72, 48 blocks of 5..40 in spans of 200 at V = 50257 59 -> 39, 16
+    // blocks of 1..100 in spans of 200 at V = 4000 34 -> 23.  Blocks of 32 lose
+    // with all positions masked (64 x 32 95 -> 101, 128 x 32 171 -> 183) and gain
+    // with few (192 with 1..4 52 -> 35); parts from several workgroups are
+    // better than either (40 full blocks of 40 82 against 97).
+    p.rows = B >= kGroups32MinB && L > 32 && L % 32 != 0 && !p.parts;
   }
   return p;
 }
@@ -1548,7 +1627,7 @@ hipError_t launch_select(fdllm_selector sel, const SelectIO& io, int B, int L, f
 
 // The kernels over evenly shared rows: whether their LDS holds the batch, and
 // the launches (one workgroup per CU, all resident).
-static constexpr size_t kRowsLdsMax = kRowsLds - 512;   // less the kernels' static part
+static constexpr size_t kRowsLdsMax = kRowsLds - 4096;   // less the kernels' static part
 
 template <class Vec>
 static bool rows_fit(int B, int L) {
@@ -1557,25 +1636,43 @@ static bool rows_fit(int B, int L) {
          nc * (long long)sizeof(RowsChunk) + (long long)rows_kept_bytes<Vec, Vec::kU>() <= (long long)kRowsLdsMax;
 }
 
-// The LDS limit is raised once per device, before the first launch there.
-template <class Vec>
-static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, const uint8_t* mask,
+// S = 1: k_rows.  The LDS limit is raised once per device, before the first
+// launch there.
+template <class Vec, int S>
+static hipError_t launch_rows_s(const void* logits, int B, int L, int nvec, const uint8_t* mask,
                                 const int32_t* bs, const int32_t* be, RowOut out, hipStream_t st) {
+  constexpr int U = S == 1 ? Vec::kU : Vec::kUSplit;
   static std::atomic<bool> allowed[64];
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  auto kernel = [] {
+    if constexpr (S == 1) return k_rows<Vec, U>;
+    else return k_rows_split<Vec, U, S>;
+  }();
   if (!allowed[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute((const void*)k_rows<Vec, Vec::kU>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowsLdsMax);
+    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowsLdsMax);
     if (e != hipSuccess) return e;
     allowed[dev].store(true, std::memory_order_release);
   }
-  const size_t lds = rows_kept_bytes<Vec, Vec::kU>() + (size_t)B * rows_chunks(L) * sizeof(RowsChunk);
-  hipLaunchKernelGGL((k_rows<Vec, Vec::kU>), dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
+  const size_t lds = rows_kept_bytes<Vec, U>() + (size_t)B * rows_chunks(L) * sizeof(RowsChunk);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
                      (const typename Vec::Mem*)logits, B, L, nvec, mask, bs, be, out);
   return hipGetLastError();
+}
+template <class Vec>
+static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, int split,
+                                const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
+                                hipStream_t st) {
+  switch (split) {
+    case 1: return launch_rows_s<Vec, 1>(logits, B, L, nvec, mask, bs, be, out, st);
+    case 2: return launch_rows_s<Vec, 2>(logits, B, L, nvec, mask, bs, be, out, st);
+    case 4: return launch_rows_s<Vec, 4>(logits, B, L, nvec, mask, bs, be, out, st);
+    case 8: return launch_rows_s<Vec, 8>(logits, B, L, nvec, mask, bs, be, out, st);
+    case 16: return launch_rows_s<Vec, 16>(logits, B, L, nvec, mask, bs, be, out, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // The vocabulary pass of a rows plan (Plan::rows): whether it can run here,
@@ -1585,15 +1682,15 @@ static bool rows_ok(const void* logits, fdllm_dtype dt, int B, int L, int V) {
   if (vec_path(logits, V, dt)) return dt == FDLLM_BF16 ? rows_fit<VecBf16x8>(B, L) : rows_fit<VecF32x4>(B, L);
   return dt == FDLLM_BF16 ? rows_fit<VecBf16Any>(B, L) : rows_fit<VecF32Any>(B, L);
 }
-static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V,
+static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V, int split,
                               const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
                               hipStream_t st) {
   if (vec_path(logits, V, dt)) {
-    if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, mask, bs, be, out, st);
-    return launch_rows_t<VecF32x4>(logits, B, L, V / 4, mask, bs, be, out, st);
+    if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, st);
+    return launch_rows_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, st);
   }
-  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16Any>(logits, B, L, V, mask, bs, be, out, st);
-  return launch_rows_t<VecF32Any>(logits, B, L, V, mask, bs, be, out, st);
+  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, st);
+  return launch_rows_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, st);
 }
 
 template <class Vec, int R, bool Robust>
@@ -1728,6 +1825,11 @@ static fdllm_status step_split(const Plan& p, fdllm_selector sel, const void* lo
   const RowOut out{tokens, conf, eps, lse};
   SelectIO io{conf, eps, mask, block_start, block_end, commit, n_commit, tokens, x, etain};
   hipError_t err;
+  if (p.rows && rows_ok(logits, dtype, B, L, V)) {
+    err = launch_rows(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, st);
+    if (err != hipSuccess) return FDLLM_ERR_HIP;
+    return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
+  }
   if (p.parts && workspace && workspace_bytes >= out_bytes_for(B, L) +
                                                      align256(n * p.parts * sizeof(WavePartial))) {
     // the rows' parts from several workgroups each, combined by the selection
@@ -1827,7 +1929,7 @@ fdllm_status fdllm_confidence(const void* logits, fdllm_dtype dtype, int B, int 
   RowOut out{tokens, conf, eps, lse};
   hipStream_t st = (hipStream_t)stream;
   if (p.rows && rows_ok(logits, dtype, B, L, V))
-    return launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, out, st) == hipSuccess
+    return launch_rows(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, st) == hipSuccess
                ? FDLLM_OK
                : FDLLM_ERR_HIP;
   // the rows of a fused step's small-batch remainder are split as the decode
@@ -1949,7 +2051,7 @@ fdllm_status decode_step(const void* logits, fdllm_dtype dtype, int B, int L, in
     char* ws = (char*)workspace;
     const RowOut o{tokens ? tokens : (int32_t*)ws, conf ? conf : (float*)(ws + n),
                    eps ? eps : (float*)(ws + 2 * n), lse};
-    if (launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, o, st) != hipSuccess)
+    if (launch_rows(logits, dtype, B, L, V, 1, mask, block_start, block_end, o, st) != hipSuccess)
       return FDLLM_ERR_HIP;
     const SelectIO io{o.conf, o.eps, mask, block_start, block_end, commit, n_commit, o.tokens, x, etain};
     return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;

@@ -572,3 +572,42 @@ def test_rows_of_any_length_and_start(gpu, V, dt):
             bad[2, 5, i] = float("inf")
             status, counts = gpu.fdllm_check_inputs(bad, mask, start, end)
             assert status == gpu.ERR_NONFINITE and counts == [0, 0, 1]
+
+
+@pytest.mark.parametrize("B,L,V,dt,window", [
+    (8, 100, 126464, torch.bfloat16, 100),     # rows split 16 ways, one team a workgroup
+    (48, 200, 50257, torch.bfloat16, 40),      # 8 ways, odd rows
+    (128, 40, 70000, torch.float32, 40),       # 4 ways
+    (200, 50, 40000, torch.bfloat16, 50),      # 2 ways
+    (60, 33, 500, torch.float32, 33),          # whole rows
+    (40, 1000, 8192, torch.bfloat16, 1000),    # more rows a team than its ring holds
+    (9, 70, 17000, torch.bfloat16, 3),         # fewer rows than workgroups
+])
+def test_shared_split_rows(gpu, B, L, V, dt, window):
+    """Split rows shared evenly by the workgroups' teams: the oracle's rows and
+    decisions, fdllm_confidence's bits in the decode step, and equal rows equal
+    bits; the last sequence has no candidate, the first an invalid window."""
+    inp = workloads.random_case(B, L, V, dt, device="cuda", seed=B + L, window=window, poison=False)
+    inp.start[0], inp.end[0] = 5, 3
+    inp.mask[B - 1] = 0
+    i0, i1 = L - 2, L - 1                          # two equal rows in two sequences
+    inp.start[2], inp.end[2], inp.start[3], inp.end[3] = i0, L, i0, L
+    inp.mask[2, i0:], inp.mask[3, i0:] = 1, 1
+    inp.logits[3, i1] = inp.logits[2, i0]
+    say(f"[shared split rows] {inp.name}")
+    ref = gpu_confidence(gpu, inp)
+    mask, x, o = _decode(gpu, inp, "profile", 1.0)
+    for name, t in zip(("tokens", "conf", "eps", "lse"), ref):
+        assert torch.equal(o[name].view(torch.int32), t.view(torch.int32)), name
+        assert t[3, i1] == t[2, i0], name
+    bs = list(range(1, min(B, 6))) + [B - 1]
+    m0, x0 = sub_mask(inp.mask.cpu().numpy(), bs), inp.x.cpu().numpy()
+    start, end = inp.start.cpu().numpy().copy(), inp.end.cpu().numpy().copy()
+    start[0], end[0] = 0, 0
+    rows = row_source(inp.logits)
+    cells = candidates(m0, start, end, bs)
+    compare_rows(*[t.cpu().numpy() for t in ref], *oracle.confidence(rows, B, L, m0, start, end), cells)
+    check_defaults(*[t.cpu().numpy() for t in ref], inp.mask.cpu().numpy(), start, end, range(B))
+    r = oracle.decode_step(rows, B, L, m0, start, end, x0, "profile", 1.0)
+    compare_selection(o["commit"].cpu().numpy(), o["n_commit"].cpu().numpy(), r.commit, r.n_commit, r.flagged, bs)
+    assert int(o["n_commit"][0]) == -1 and int(o["n_commit"][B - 1]) == 0
