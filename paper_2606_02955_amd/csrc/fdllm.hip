@@ -1305,8 +1305,8 @@ k_rows(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
                       });
 }
 
-// The same for rows split over S waves: a workgroup's kRowsWaves / S teams take
-// its rows in turn, every wave its part of a row, and the last wave of a team
+// The same for rows split over S waves: workgroup g of n takes every n-th row,
+// its kRowsWaves / S teams in turn, every wave its part of a row, and the last wave of a team
 // to finish a row combines the parts, as k_confidence would (the same bits);
 // the others are at the team's next row by then.  A team's parts wait in a
 // ring of kRowsRing rows.
@@ -1333,14 +1333,17 @@ k_rows_split(const typename Vec::Mem* __restrict__ logits, int B, int L, int nve
   const int total = rows_find(chunk, s_wave, B, L, mask, bstart, bend);
   rows_defaults(chunk, B, L, out);
   const int nc = B * rows_chunks(L);
-  const int r0 = __builtin_amdgcn_readfirstlane((int)((long long)blockIdx.x * total / gridDim.x));
-  const int r1 = __builtin_amdgcn_readfirstlane((int)((long long)(blockIdx.x + 1) * total / gridDim.x));
-  int r = r0 + team;
-  if (r >= r1) return;
-  int k = rows_search(chunk, nc, r);
-  for (int step = 0; r < r1; r += kTeams, ++step) {
-    while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
-    k = __builtin_amdgcn_readfirstlane(k);
+  for (int step = 0;; ++step) {
+    // every (workgroups)-th row, the workgroup's teams in turn: the chip moves
+    // through the rows as one front.  A contiguous share per workgroup takes
+    // the same time on buffers in use, but the first pass over new ones waits
+    // for each CU's own pages: 100 blocks of 8..48, float32, V = 126464 236
+    // against 234 us, new buffers 326 against 297.  (k_rows keeps contiguous
+    // shares: 300 blocks of 32..128 281 against 295 us, new buffers 376 against
+    // 356; 456 before either.)
+    const int r = (step * kTeams + team) * (int)gridDim.x + (int)blockIdx.x;
+    if (r >= total) return;
+    const int k = __builtin_amdgcn_readfirstlane(rows_search(chunk, nc, r));
     const int slot = rows_slot(chunk[k], r);
     const WavePartial wp = row_pass<Vec, U, S>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, w,
                                                s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
