@@ -267,7 +267,10 @@ fdllm_status fdllm_decode_step_static(const void* logits, fdllm_dtype dtype, int
  * The logits of candidate position (b, i) are l_v = sum_k h[b,i,k] W[v,k],
  * formed on the matrix cores with float32 accumulation (bf16 operands) and
  * folded into the online (max, sum, argmax) of the vocabulary pass; no logit
- * is stored.  Equal weight rows have equal logits, bit for bit, in a call.
+ * is stored.  Equal weight rows have equal logits, bit for bit, in a call, and
+ * equal hidden rows equal outputs.  A row's last bits may depend on how many
+ * candidates the call has (the vocabulary is divided by that number), not on
+ * which they are or on where it is among them.
  * From the logits on, the outputs are those of fdllm_confidence (token,
  * conf, eps, lse; defaults for non-candidates).
  *   hidden [B, L, d] bf16, 16-byte aligned (in): final hidden states;

@@ -28,6 +28,7 @@
 #include <atomic>
 
 #include "fdllm.h"
+#include "lm_work.h"
 #include "pass_common.h"
 
 namespace fdllm {
@@ -43,9 +44,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kLmWaves = 8;                    // waves per workgroup
 constexpr int kLmThreads = kLmWaves * kWave;
 
-// Candidate rows of every sequence, compacted (any order: a row's result
-// does not depend on where it sits in a tile); default outputs for
-// every other position.  One wavefront per sequence.
+// Candidate rows of every sequence, compacted (in any order, from run to run
+// too: a row's result depends neither on its place in a tile nor on the tile,
+// all tiles meet the same vocabulary ranges); default outputs for every other
+// position.  One wavefront per sequence.
 __global__ void __launch_bounds__(256)
 k_lm_compact(const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
              const int32_t* __restrict__ bend, int B, int L, int32_t* __restrict__ rows,
@@ -216,64 +218,28 @@ __device__ __forceinline__ void lm_combine(LmState& st, float M2, float K2, doub
 }
 
 // ---- work division ----------------------------------------------------------
-// The number of candidates is on the device, so the division of the work is
-// too: kLmGroups workgroups (one per compute unit) read it and share the
-// (position tile, vocabulary range) plane evenly, whatever the span.  The
-// candidates are cut into the fewest tiles of at most 256 positions, and the
-// tiles are as narrow (32, 64, 128, 192, 256 positions) as then still holds
-// them: a narrow tile saves the matrix work and the reads of the hidden
-// states of positions that are not there.  With one position tile the
-// vocabulary is divided in steps of 16 rows, so every workgroup reads the
-// same number of weight rows; with several, in whole weight tiles, the
-// position tiles one after the other, so that the workgroups on the same
-// weight rows sit on the same XCD (their distance is a multiple of eight for
-// 2^k position tiles).
-constexpr int kLmGroups = 256;
-constexpr int kLmVt = 256;                     // vocabulary rows per tile (MFMA A operand)
-constexpr int kLmMaxPt = 256;                  // positions per tile at most (MFMA B operand)
-
-struct LmWork {
-  int mt, pt;        // position tiles and their width
-  int unit, nb;      // vocabulary rows per unit, units of the vocabulary
-  int groups;        // workgroups that have work
-};
-
-__host__ __device__ inline LmWork lm_work(int n, int V) {
-  LmWork w;
-  w.mt = (n + kLmMaxPt - 1) / kLmMaxPt;
-  const int per = w.mt ? (n + w.mt - 1) / w.mt : 0;
-  w.pt = per <= 32 ? 32 : per <= 64 ? 64 : per <= 128 ? 128 : per <= 192 ? 192 : 256;
-  w.unit = w.mt > 1 ? kLmVt : 16;
-  w.nb = (V + w.unit - 1) / w.unit;
-  const long long t = (long long)w.mt * w.nb;
-  w.groups = t < kLmGroups ? (int)t : kLmGroups;
+// lm_work (lm_work.h) on the device, the candidates' number of rounds a lane
+// each; every kernel of a call forms the same division for itself.
+__device__ __forceinline__ LmWork lm_work_device(int n, int V, int d) {
+  LmWork w = lm_work_tiles(n, V);
+  if (w.mt > 1) {
+    const int lane = lane_id();
+    int k = lm_round_ranges(w, lane % kLmRounds);
+    unsigned long long t = lm_round_time(w, k, d);
+    int at = lane % kLmRounds;                  // the first of the shortest, as lm_work
+#pragma unroll
+    for (int x = 1; x < kLmRounds; x <<= 1) {
+      const unsigned long long t2 = __shfl_xor(t, x);
+      const int k2 = __shfl_xor(k, x), at2 = __shfl_xor(at, x);
+      if (t2 < t || (t2 == t && at2 < at)) {
+        t = t2;
+        k = k2;
+        at = at2;
+      }
+    }
+    w.k = __builtin_amdgcn_readfirstlane(k);
+  }
   return w;
-}
-// first unit of workgroup g (units of all position tiles, one tile after the
-// other), floor(g T / groups) for T units; workgroup g takes
-// [lm_first(g), lm_first(g + 1)).  No division: fewer units than workgroups
-// are one each, else groups is a power of two.
-static_assert((kLmGroups & (kLmGroups - 1)) == 0, "shifts in lm_first");
-__host__ __device__ inline long long lm_first(const LmWork& w, int g) {
-  if (w.groups < kLmGroups) return g;
-  const long long t = (long long)w.mt * w.nb;
-  return g * (t / kLmGroups) + g * (t % kLmGroups) / kLmGroups;
-}
-// the workgroup that holds unit u: the largest g with lm_first(g) <= u
-__host__ __device__ inline int lm_owner(const LmWork& w, long long u) {
-  if (w.groups < kLmGroups) return (int)u;
-  if (w.mt == 1) return u == 0 ? 0 : u == w.nb - 1 ? kLmGroups - 1 : (int)(((u + 1) * kLmGroups - 1) / w.nb);
-  return (int)(((u + 1) * kLmGroups - 1) / ((long long)w.mt * w.nb));
-}
-// partials per position: the workgroups that a position tile can meet
-__host__ __device__ inline int lm_stride(const LmWork& w) {
-  return w.mt <= 1 ? w.groups : w.groups / w.mt + 2;
-}
-// most partials that any number of candidates up to n needs
-static size_t lm_max_partials(long long n) {
-  const long long one = (n < kLmMaxPt ? n : kLmMaxPt) * (long long)kLmGroups;
-  const long long mt = (n + kLmMaxPt - 1) / kLmMaxPt;
-  return (size_t)(one + (mt > 1 ? mt * kLmMaxPt * 2 : 0));
 }
 
 // ---- LDS-DMA main loop -----------------------------------------------------
@@ -727,20 +693,24 @@ __device__ __forceinline__ void lm_segment(const LmArgs& a, const int32_t* rows,
 // leave at once): in one kernel the wide tiles' registers made the narrow
 // ones reload spilled values in the fold, and such a reload waits for every
 // weight load in flight.
-template <class F>
+// One: a single position tile, so one segment at most (a loop here made
+// k_lm_wide<true> spill registers).
+template <bool One, class F>
 __device__ __forceinline__ void lm_segments(const LmArgs& a, const LmWork& w, int n, F&& segment) {
   const int g = blockIdx.x;
-  const int p_last = w.mt == 1 ? 0 : (int)((lm_first(w, g + 1) - 1) / w.nb);
-  for (int p = w.mt == 1 ? 0 : (int)(lm_first(w, g) / w.nb); p <= p_last; ++p) {
-    const long long u0 = (long long)p * w.nb;
-    const int b0 = (int)max(0ll, lm_first(w, g) - u0), b1 = (int)min((long long)w.nb, lm_first(w, g + 1) - u0);
+  const int end = lm_seg_end(w, g);
+  int u = lm_seg_first(w, g);
+  if (u >= end) return;
+  do {
     // uniform values out of divisions: scalar registers
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    const int p0 = uni(p * w.pt), cnt = uni(min(w.pt, n - p0));
-    const int v_beg = uni(b0 * w.unit), v_end = uni(min(a.V, b1 * w.unit));
-    const int split = uni(g - lm_owner(w, u0)), stride = uni(lm_stride(w));
-    segment(p0, cnt, v_beg, v_end, stride, split);
-  }
+    const int s = One ? u : uni(u / w.mt);
+    const int p0 = One ? 0 : uni((u - s * w.mt) * w.pt), cnt = One ? n : uni(min(w.pt, n - p0));
+    const int v_beg = uni(lm_first(w, s) * w.unit);
+    const int v_end = uni((int)min((long long)a.V, (long long)lm_first(w, s + 1) * w.unit));
+    segment(p0, cnt, v_beg, v_end, w.k, s);
+    u += kLmGroups / kLmXcds;
+  } while (!One && u < end);
 }
 
 // The candidate positions, in position order, found by every workgroup for
@@ -821,11 +791,10 @@ __global__ void __launch_bounds__(kLmThreads) k_lm_narrow(LmArgs a, LmCand c) {
   else n = *a.count;
   n = __builtin_amdgcn_readfirstlane(n);
   if (n == 0 || n > kLmNarrow) return;
-  const LmWork w = lm_work(n, a.V);
-  if ((int)blockIdx.x >= w.groups) return;
+  const LmWork w = lm_work_tiles(n, a.V);
   const int32_t* rows = Self ? list : a.rows;
   const int flip = lm_flip((int)blockIdx.x, a.d / kLmBK);
-  lm_segments(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
+  lm_segments<true>(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
     if (w.pt == 32) lm_segment<LmShape<32, 8, 4, 4>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
     else if (w.pt == 64) lm_segment<LmShape<64, 8, 3, 3>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
     else lm_segment<LmShape<128, 4, 3, 3>, true>(a, rows, p0, cnt, v_beg, v_end, flip, stride, split);
@@ -839,9 +808,8 @@ __global__ void __launch_bounds__(kLmThreads)
 k_lm_wide(LmArgs a) {
   const int n = __builtin_amdgcn_readfirstlane(*a.count);
   if (One ? (n <= 128 || n > kLmMaxPt) : n <= kLmMaxPt) return;
-  const LmWork w = lm_work(n, a.V);
-  if ((int)blockIdx.x >= w.groups) return;
-  lm_segments(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
+  const LmWork w = One ? lm_work_tiles(n, a.V) : lm_work_device(n, a.V, a.d);
+  lm_segments<One>(a, w, n, [&](int p0, int cnt, int v_beg, int v_end, int stride, int split) {
     if (w.pt == 192) lm_segment<LmShape<192, 2, 3, 2>, One>(a, a.rows, p0, cnt, v_beg, v_end, 0, stride, split);
     else lm_segment<LmShape<256, 2, 3, 2>, One>(a, a.rows, p0, cnt, v_beg, v_end, 0, stride, split);
   });
@@ -1065,7 +1033,7 @@ k_lm_stream(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ we
 // of the row's contiguous partials, all loaded at once, then a fixed
 // butterfly over the lanes (both partners of every step form the same sum)
 // and the finish.
-constexpr int kLmFinishPer = (kLmGroups + 2 + kWave - 1) / kWave;   // partials per lane at most
+constexpr int kLmFinishPer = kLmGroups / kWave;   // partials per lane at most
 __device__ __forceinline__ void lm_finish_row(const WavePartial* p, int n_split, int row, RowOut out) {
   const int lane = threadIdx.x % kWave;
   WavePartial q[kLmFinishPer];
@@ -1094,14 +1062,12 @@ __device__ __forceinline__ void lm_finish_row(const WavePartial* p, int n_split,
 
 __global__ void __launch_bounds__(256)
 k_lm_finish(const int32_t* __restrict__ rows, const int32_t* __restrict__ count,
-            const WavePartial* __restrict__ partials, int V, RowOut out) {
-  const int k = blockIdx.x * 4 + threadIdx.x / kWave;
+            const WavePartial* __restrict__ partials, int d, int V, RowOut out) {
+  const int r = blockIdx.x * 4 + threadIdx.x / kWave;
   const int n = *count;
-  if (k >= n) return;
-  const LmWork w = lm_work(n, V);
-  const long long u0 = (long long)(k / w.pt) * w.nb;
-  const int n_split = lm_owner(w, u0 + w.nb - 1) - lm_owner(w, u0) + 1;
-  lm_finish_row(partials + (size_t)k * lm_stride(w), n_split, rows[k], out);
+  if (r >= n) return;
+  const int k = lm_work_device(n, V, d).k;
+  lm_finish_row(partials + (size_t)r * k, k, rows[r], out);
 }
 
 // the same for the streaming kernel's partials, n_split of every row
@@ -1147,7 +1113,7 @@ static LmPlan lm_plan(int B, int L, int d, int V, bool need_out) {
   p.stream = lm_streams(n, d);
   const int nblk = (V + kLsBlk - 1) / kLsBlk;
   p.n_split = nblk < kLmGroups ? nblk : kLmGroups;
-  const size_t partials = p.stream ? (size_t)n * p.n_split : lm_max_partials(n);
+  const size_t partials = p.stream ? (size_t)n * p.n_split : lm_max_partials(n, V);
   p.off_rows = 256;
   p.off_partials = p.off_rows + align256((size_t)n * 4);
   p.off_out = p.off_partials + align256(partials * sizeof(WavePartial));
@@ -1236,7 +1202,7 @@ static hipError_t lm_launch(const void* hidden, const void* weight, int B, int L
     if (n > kLmNarrow) hipLaunchKernelGGL(k_lm_wide<true>, grid, block, kLmLdsBytes, st, a);
     if (n > kLmMaxPt) hipLaunchKernelGGL(k_lm_wide<false>, grid, block, kLmLdsBytes, st, a);
     hipLaunchKernelGGL(k_lm_finish, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, rows, count, part,
-                       V, out);
+                       d, V, out);
   }
   return hipGetLastError();
 }

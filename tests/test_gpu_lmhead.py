@@ -262,3 +262,41 @@ def test_lmhead_equal_weight_rows_tie(gpu, B, L, d, V):
     end = torch.full((B,), L, dtype=torch.int32, device="cuda")
     tok = _gpu_conf(gpu, hidden, weight, mask, start, end)[0].cpu()
     assert torch.equal(tok, target.to(torch.int32))
+
+
+@pytest.mark.parametrize("B,L,n,d,V", [(20, 32, 640, 64, 126464), (88, 32, 2816, 64, 126464), (40, 64, 1281, 192, 30011)])
+def test_lmhead_equal_hidden_rows(gpu, B, L, n, d, V):
+    """General values, the same 256 hidden states in every position tile: their
+    outputs are the same bits, whichever tile they are in."""
+    say(f"[lmhead equal hidden rows] candidates={n} d={d} V={V}")
+    g = torch.Generator().manual_seed(n)
+    weight = torch.randn((V, d), generator=g).to(torch.bfloat16).cuda()
+    some = torch.randn((256, d), generator=g).to(torch.bfloat16).cuda() * d ** -0.5
+    mask = torch.zeros(B * L, dtype=torch.uint8)
+    mask[:n] = 1
+    hidden = some[torch.arange(B * L) % 256].view(B, L, d).contiguous()
+    start = torch.zeros(B, dtype=torch.int32, device="cuda")
+    end = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    out = _gpu_conf(gpu, hidden, weight, mask.view(B, L).cuda(), start, end)
+    for name, t in zip(("tokens", "conf", "eps", "lse"), out):
+        rows = t.view(-1)[:n].view(torch.int32)
+        same = rows == rows[torch.arange(n) % 256]
+        assert bool(same.all()), (name, int((~same).sum()))
+
+
+@pytest.mark.parametrize("B,L,blk,d,V", [(300, 64, 10, 64, 126464), (33, 250, 250, 64, 50257), (48, 64, 32, 1024, 9000)])
+def test_lmhead_bitwise_reproducible(gpu, B, L, blk, d, V):
+    """The same call five times: the same bits, also where the candidates are
+    listed in another order from run to run (more than 8192 positions)."""
+    say(f"[lmhead reproducible] B={B} L={L} blk={blk} d={d} V={V}")
+    g = torch.Generator().manual_seed(V)
+    weight = torch.randn((V, d), generator=g).to(torch.bfloat16).cuda()
+    hidden = (torch.randn((B, L, d), generator=g) * d ** -0.5).to(torch.bfloat16).cuda()
+    mask = torch.ones((B, L), dtype=torch.uint8, device="cuda")
+    start = torch.zeros(B, dtype=torch.int32, device="cuda")
+    end = torch.full((B,), blk, dtype=torch.int32, device="cuda")
+    first = _gpu_conf(gpu, hidden, weight, mask, start, end)
+    for k in range(4):
+        for name, t, r in zip(("tokens", "conf", "eps", "lse"), _gpu_conf(gpu, hidden, weight, mask, start, end), first):
+            differ = t.view(torch.int32) != r.view(torch.int32)
+            assert not bool(differ.any()), (k, name, int(differ.sum()))
