@@ -1225,13 +1225,16 @@ __device__ __forceinline__ int rows_find(RowsChunk* chunk, int* s_wave, int B, i
   return total;
 }
 
-// The default outputs of the non-candidates, shared by all workgroups.
+// The default outputs of the non-candidates, shared by all workgroups.  The
+// positions are unsigned: a stride past the last of them (at most 2^31 - 1)
+// still fits.
 __device__ __forceinline__ void rows_defaults(const RowsChunk* chunk, int B, int L, const RowOut& out) {
-  const int C = rows_chunks(L), slots = B * L;
-  for (int p = blockIdx.x * kRowsThreads + (int)threadIdx.x; p < slots; p += gridDim.x * kRowsThreads) {
-    const int b = (int)((unsigned)p / (unsigned)L);
+  const int C = rows_chunks(L);
+  const unsigned slots = (unsigned)B * (unsigned)L;
+  for (unsigned p = blockIdx.x * kRowsThreads + threadIdx.x; p < slots; p += gridDim.x * kRowsThreads) {
+    const int b = (int)(p / (unsigned)L);
     const int first = chunk[b * C].first;      // of the window; an empty one has no candidates
-    const int rel = p - first;
+    const int rel = (int)p - first;
     const bool in = rel >= 0 && rel < C * kWave && first >= b * L;
     const unsigned long long word = in ? chunk[b * C + rel / kWave].word : 0ull;
     if (((word >> (rel % kWave)) & 1ull) == 0ull) store_default(out, (size_t)p);

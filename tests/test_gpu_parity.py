@@ -611,3 +611,28 @@ def test_shared_split_rows(gpu, B, L, V, dt, window):
     r = oracle.decode_step(rows, B, L, m0, start, end, x0, "profile", 1.0)
     compare_selection(o["commit"].cpu().numpy(), o["n_commit"].cpu().numpy(), r.commit, r.n_commit, r.flagged, bs)
     assert int(o["n_commit"][0]) == -1 and int(o["n_commit"][B - 1]) == 0
+
+
+def test_shared_rows_longest_span(gpu):
+    """As many positions as the shared rows' plan takes, 8 short of 2^31: the
+    defaults reach the last of them and nothing past it."""
+    B, L, V = 8, 268435455, 1
+    say(f"[shared rows] B={B} L={L} V={V}")
+    logits = torch.zeros((B, L, V), dtype=torch.bfloat16, device="cuda")
+    mask = torch.zeros((B, L), dtype=torch.uint8, device="cuda")
+    start = torch.tensor([0, 5, 64, L - 1024, 0, L - 1, 7, L - 3], dtype=torch.int32, device="cuda")
+    end = torch.tensor([3, 5, 1088, L, 1, L, 6, L], dtype=torch.int32, device="cuda")      # 6: invalid
+    for b in range(B):
+        mask[b, int(start[b])] = 1
+    mask[B - 1, L - 1] = 1
+    buf = torch.full((B * L + 1024,), -7, dtype=torch.int32, device="cuda")
+    tokens = buf[:B * L].view(B, L)
+    gpu.fdllm_confidence(logits, mask, start, end, tokens, *[torch.full((B, L), -7.0, device="cuda")])
+    torch.cuda.synchronize()
+    want = torch.full((B, L), -1, dtype=torch.int32, device="cuda")
+    for b in range(B):
+        if b not in (1, 6):
+            want[b, int(start[b])] = 0
+    want[B - 1, L - 1] = 0
+    assert torch.equal(tokens, want)
+    assert bool((buf[B * L:] == -7).all())
