@@ -35,6 +35,8 @@ HIPCC_FLAGS = [
     # -mno-amdgpu-ieee: the device library keeps IEEE mode, and its work-item
     # and workgroup id functions would then stay out-of-line calls.)
     "-Xarch_device", "-fno-honor-nans",
+    # a pointer passed on with less alignment than its type promises
+    "-Werror=align-mismatch",
     "-Wno-unused-command-line-argument",
 ]
 

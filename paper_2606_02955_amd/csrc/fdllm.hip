@@ -190,8 +190,10 @@ __device__ __forceinline__ const typename Vec::Mem* row_at(const typename Vec::M
     return logits + slot * (size_t)n;
 }
 
-template <class Mem>
-__device__ __forceinline__ u32x4 load_stream(const Mem* p) {
+// (by the format: a deduced pointee would lose the alignment of Vec::Mem, and
+// the load would promise 16 bytes)
+template <class Vec>
+__device__ __forceinline__ typename Vec::Raw load_stream(const typename Vec::Mem* p) {
   return __builtin_nontemporal_load(p);
 }
 
@@ -282,14 +284,14 @@ __device__ __forceinline__ WavePartial row_pass(const typename Vec::Mem* __restr
   const int nbf = njf / U;
   auto load_full = [&](Raw (&r)[U], int jb) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[u] = load_stream(p + (jb * U + u) * kStride);
+    for (int u = 0; u < U; ++u) r[u] = load_stream<Vec>(p + (jb * U + u) * kStride);
   };
   auto load_part = [&](Raw (&r)[U], int jb) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = jb * U + u;
       const int v = (w + j * S) * kWave + lane;
-      r[u] = (j < nj && v < nwhole) ? load_stream(p + j * kStride) : Vec::pad();
+      r[u] = (j < nj && v < nwhole) ? load_stream<Vec>(p + j * kStride) : Vec::pad();
       if constexpr (Vec::kAny) {
         if (j < nj && v == nwhole && v < nvec)
           r[u] = Vec::tail(reinterpret_cast<const typename Vec::Elem*>(row) + (size_t)v * E, n - v * E);
@@ -1418,7 +1420,7 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Mem* __restri
   const typename Vec::Mem* row = row_at<Vec>(logits, (size_t)slot, nvec);
   bool bad = false;
   const int nwhole = Vec::kAny ? nvec / Vec::kElems : nvec;
-  for (int v = lane; v < nwhole; v += kWave) bad |= Vec::bad(load_stream(row + v));
+  for (int v = lane; v < nwhole; v += kWave) bad |= Vec::bad(load_stream<Vec>(row + v));
   if constexpr (Vec::kAny) {
     const int i = nwhole * Vec::kElems + lane;
     if (i < nvec) bad |= bad_bits(Vec::f32_bits(reinterpret_cast<const typename Vec::Elem*>(row)[i]));
