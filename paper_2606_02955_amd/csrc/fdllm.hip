@@ -1794,10 +1794,10 @@ static bool sizes_ok(int B, int L, int V) {
 // wave partials of the parts plan
 static size_t out_bytes_for(int B, int L) { return 3 * align256((size_t)B * (size_t)L * 4); }
 static size_t workspace_bytes_for(int B, int L, const Plan& p) {
-  // evenly shared rows: the outputs that the caller does not take (without a
-  // place for them, one workgroup per sequence); none where no device tells
-  // how many workgroups there would be
-  if (p.rows) return device_cus() > 0 ? out_bytes_for(B, L) : 0;
+  // evenly shared rows: the outputs that the caller does not take, whether a
+  // device is visible or not (from 256 sequences the step runs without a place
+  // for them, one workgroup per sequence)
+  if (p.rows) return out_bytes_for(B, L);
   if (p.fused) {
     if (!p.rem) return 0;
     const size_t n = (size_t)p.rem * (size_t)L;

@@ -278,9 +278,11 @@ def test_workspace_sizes_follow_the_plans(lib):
     assert small >= 3 * 32 * 4 + 32 * 16 * 24
     # a long span (L > 64) keeps single-workgroup rows: outputs only
     assert _ws(lib.fdllm_workspace_size, 8, 256, V, 0) < 3 * 8 * 256 * 4 + 1024 * 3
-    # one workgroup per sequence (no workspace) from 256 sequences on
-    assert _ws(lib.fdllm_workspace_size, 255, 32, V, 0) >= 3 * 255 * 32 * 4
-    assert _ws(lib.fdllm_workspace_size, 256, 32, V, 0) == 0
+    # shared rows, by two kernels: tokens, conf and eps pass through memory
+    for B, L in [(255, 32), (256, 32), (767, 32), (48, 200), (9, 70)]:
+        assert 3 * B * L * 4 <= _ws(lib.fdllm_workspace_size, B, L, 50257, 0) < 3 * (B * L * 4 + 256)
+    # one workgroup per sequence (no workspace) from 768 sequences on
+    assert _ws(lib.fdllm_workspace_size, 768, 32, V, 0) == 0
     # LM head: up to 32 positions need no partial logits
     s32 = _ws(lib.fdllm_lmhead_workspace_size, 1, 32, 4096, V)
     assert s32 < 4 << 20
