@@ -1118,11 +1118,6 @@ static LmPlan lm_plan(int B, int L, int d, int V, bool need_out) {
   p.off_partials = p.off_rows + align256((size_t)n * 4);
   p.off_out = p.off_partials + align256(partials * sizeof(WavePartial));
   p.bytes = p.off_out + (need_out ? 3 * align256((size_t)n * 4) : 0);
-  // the size that the interface states for these shapes (two halves of the
-  // hidden dimension, 64 float32 logits per vocabulary entry each); the tiles
-  // use the front of it
-  if (n > kLsRows && n <= 64 && d % 1024 == 0 && d <= kLsMaxD)
-    p.bytes += align256((size_t)2 * V * 64 * sizeof(float));
   return p;
 }
 

@@ -270,8 +270,7 @@ def _ws(fn, *args):
 def test_workspace_sizes_follow_the_plans(lib):
     """Host planning, seen through the workspace queries: small batches with
     blocks of at most one wavefront reserve room for the rows' wave partials
-    (24 bytes each); the LM head's two-part plan (33..64 positions, d a
-    multiple of 1024) reserves the two halves' partial logits."""
+    (24 bytes each), and the LM head for its vocabulary ranges' states."""
     V = 126464
     # decode step: B=1, L=32 bf16 rows split 16 ways -> 32 x 16 partials
     small = _ws(lib.fdllm_workspace_size, 1, 32, V, 0)
@@ -283,13 +282,11 @@ def test_workspace_sizes_follow_the_plans(lib):
         assert 3 * B * L * 4 <= _ws(lib.fdllm_workspace_size, B, L, 50257, 0) < 3 * (B * L * 4 + 256)
     # one workgroup per sequence (no workspace) from 768 sequences on
     assert _ws(lib.fdllm_workspace_size, 768, 32, V, 0) == 0
-    # LM head: up to 32 positions need no partial logits
-    s32 = _ws(lib.fdllm_lmhead_workspace_size, 1, 32, 4096, V)
-    assert s32 < 4 << 20
-    # 64 positions: 2 halves x V x 64 float32 partial logits
-    s64 = _ws(lib.fdllm_lmhead_workspace_size, 2, 32, 4096, V)
-    assert s64 >= 2 * V * 64 * 4
-    # 64 positions with d not a multiple of 1024: the tiled plan, no partial logits
-    assert _ws(lib.fdllm_lmhead_workspace_size, 2, 32, 4032, V) < 2 * V * 64 * 4
-    # 65 positions: the tiled plan
-    assert _ws(lib.fdllm_lmhead_workspace_size, 1, 65, 4096, V) < 2 * V * 64 * 4
+    # LM head: the candidates' list, the partial results (24 bytes for each of
+    # at most 256 vocabulary ranges a position) and the outputs, no logits
+    for B, L, d in [(1, 32, 4096), (2, 32, 4096), (2, 32, 4032), (1, 65, 4096), (8, 32, 4096)]:
+        n = B * L
+        least = n * 256 * 24 + 4 * 4 * n
+        assert least <= _ws(lib.fdllm_lmhead_workspace_size, B, L, d, V) < least + 6 * 256
+    # beyond one position tile, several ranges a workgroup at most
+    assert _ws(lib.fdllm_lmhead_workspace_size, 128, 256, 1024, V) < 16 << 20

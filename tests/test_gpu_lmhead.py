@@ -40,7 +40,7 @@ CASES = [
     (4, 8, 1024, 2500, "exact", 5),          # several sequences, windows inside them
     (1, 1, 512, 100, "exact", 1),            # a single position
     (1, 32, 64, 1000, "exact", 32),          # d not a multiple of 512: the tiled kernel
-    # 33..64 positions, d a multiple of 1024: the k-split kernel
+    # 33..64 positions, d a multiple of 1024
     (2, 32, 4096, 126464, "exact", 32),      # two sequences' blocks at LLaDA's sizes
     (1, 64, 1024, 3001, "random", 64),
     (2, 20, 3072, 999, "exact", 20),
