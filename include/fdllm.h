@@ -193,7 +193,7 @@ fdllm_status fdllm_reveal(const uint8_t* commit, const int32_t* tokens, int32_t*
  * one (one workgroup per sequence).  Between, the rows of all sequences are
  * shared evenly by the chip and the selection is a second kernel; that needs
  * the workspace, or tokens, conf and eps all given, and a span of at most
- * about 3800 / B 64-position pieces; otherwise one workgroup per sequence, with
+ * about 5600 / B 64-position pieces; otherwise one workgroup per sequence, with
  * the same bits.  When a batch of 768 or more exceeds a multiple of the GPU's
  * compute-unit count by at most 64 sequences, those last sequences run with
  * the small-batch kernels on a stream the library keeps per device, at the

@@ -458,16 +458,277 @@ __device__ __forceinline__ RowResult combine_parts(const WavePartial* part) {
   return combine_parts_regs<S>(p);
 }
 
+// ---- candidate rows by their number -----------------------------------------
+// 64 window positions of a sequence
+struct RowsChunk {
+  unsigned long long word;   // candidates among them
+  int first;                 // slot of the first position
+  int before;                // candidates of all chunks before
+};
+
+// 64-position chunks of a sequence's window at most
+__host__ __device__ inline int rows_chunks(int L) { return ((L < kMaxBlock ? L : kMaxBlock) + kWave - 1) / kWave; }
+struct RowsWindow {
+  int slot, len;             // slot of the first position, positions
+};
+
+// Which of `n` positions (at most 64) from `slot` on are masked, one bit each,
+// by one lane: 16 bytes a load, from any byte on.  `slots` (at least 16) mask
+// bytes in all: a load that would pass the last of them starts earlier.
+__device__ __forceinline__ unsigned long long rows_word(const uint8_t* __restrict__ mask, int slot, int n,
+                                                        int slots) {
+  u32x4 v[kWave / 16];
+  int late[kWave / 16];
+#pragma unroll
+  for (int i = 0; i < kWave / 16; ++i) {
+    const int at = slot + (16 * i < n ? 16 * i : 0);
+    late[i] = max(0, at - (slots - 16));
+    __builtin_memcpy(&v[i], mask + (at - late[i]), 16);
+  }
+  unsigned long long word = 0;
+#pragma unroll
+  for (int i = 0; i < kWave / 16; ++i) {
+    unsigned bits = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      // bit 7 of every byte that is not 0, then the four of them together
+      unsigned x = ((((v[i][j] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v[i][j]) & 0x80808080u) >> 7;
+      x = (x | (x >> 7) | (x >> 14) | (x >> 21)) & 15u;
+      bits |= x << (4 * j);
+    }
+    word |= (unsigned long long)(bits >> late[i]) << (16 * i);
+  }
+  return n >= kWave ? word : word & ((1ull << n) - 1ull);
+}
+
+// Every chunk's candidates and their running counts, for the windows win(j),
+// j < n, of at most C chunks each, by a workgroup of NW waves, a lane a chunk;
+// returns the number of candidates.  Three round trips to memory and LDS in
+// all: the windows, the mask bytes, the counts.  (A wave a chunk, by a ballot,
+// is 40 instructions for each chunk, and every workgroup finds all of them:
+// 250 blocks of 50..100 rows of V = 8000 105 against 86 us, 300 blocks of
+// 32..128 at V = 32000 279 against 268.)
+template <int NW, class Win>
+__device__ __forceinline__ int rows_find(RowsChunk* chunk, int* s_wave, int n_seq, Win&& win, int C,
+                                         const uint8_t* __restrict__ mask, int slots) {
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  constexpr int NT = NW * kWave;
+  const int nc = n_seq * C;
+  for (int k = tid; k < nc; k += NT) {
+    const int j = (int)((unsigned)k / (unsigned)C), c = k - j * C;
+    const RowsWindow w = win(j);
+    const int n = max(0, min(w.len - c * kWave, kWave));
+    const int first = n > 0 ? w.slot + c * kWave : 0;
+    chunk[k].first = first;
+    chunk[k].word = n > 0 ? rows_word(mask, first, n, slots) : 0ull;
+  }
+  __syncthreads();
+  // running counts: thread t takes the chunks [t per, (t + 1) per)
+  const int per = (nc + NT - 1) / NT;
+  int own = 0;
+  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) own += __popcll(chunk[k].word);
+  int incl = own;
+#pragma unroll
+  for (int x = 1; x < kWave; x <<= 1) {
+    const int o = __shfl_up(incl, x);
+    if (lane >= x) incl += o;
+  }
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int run = incl - own, total = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) run += s_wave[w];
+    total += s_wave[w];
+  }
+  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) {
+    chunk[k].before = run;
+    run += __popcll(chunk[k].word);
+  }
+  __syncthreads();
+  return total;
+}
+
+// The default outputs of these sequences' non-candidates, shared by `groups`
+// workgroups of NW waves.  The positions are unsigned: a stride past the last
+// of them (at most 2^31 - 1) still fits.
+template <int NW, class Seq>
+__device__ __forceinline__ void rows_defaults(const RowsChunk* chunk, int n_seq, Seq&& seq, int L, int C,
+                                              unsigned group, unsigned groups, const RowOut& out) {
+  constexpr unsigned NT = NW * kWave;
+  const unsigned slots = (unsigned)n_seq * (unsigned)L;
+  for (unsigned p = group * NT + threadIdx.x; p < slots; p += groups * NT) {
+    const int j = (int)(p / (unsigned)L);
+    const int row0 = seq(j) * L;
+    const int slot = row0 + (int)(p - (unsigned)j * (unsigned)L);
+    const int first = chunk[j * C].first;      // of the window; an empty one has no candidates
+    const int rel = slot - first;
+    const bool in = rel >= 0 && rel < C * kWave && first >= row0;
+    const unsigned long long word = in ? chunk[j * C + rel / kWave].word : 0ull;
+    if (((word >> (rel % kWave)) & 1ull) == 0ull) store_default(out, (size_t)slot);
+  }
+}
+
+// The last chunk of [0, nc) with before <= r: every lane looks at one of 64
+// places, two rounds for up to 4096 chunks.
+__device__ __forceinline__ int rows_search(const RowsChunk* chunk, int nc, int r) {
+  const int lane = threadIdx.x % kWave;
+  int lo = 0, n = nc;
+  while (n > 1) {
+    const int step = (n + kWave - 1) / kWave, at = lane * step;
+    const unsigned long long le = __ballot(at < n && chunk[lo + (at < n ? at : 0)].before <= r);   // lane 0 at least
+    const int last = (kWave - 1 - (int)__builtin_clzll(le)) * step;
+    lo += last;
+    n = min(step, n - last);
+  }
+  return lo;
+}
+
+// The slot of row r: the (r - before)-th candidate of its chunk.
+__device__ __forceinline__ int rows_slot(const RowsChunk& c, int r) {
+  const int lane = threadIdx.x % kWave;
+  const int rank = __popcll(c.word & ((1ull << lane) - 1ull));
+  const int pos = (int)__builtin_ctzll(__ballot(((c.word >> lane) & 1ull) && rank == r - c.before));
+  return __builtin_amdgcn_readfirstlane(c.first + pos);
+}
+
+// Streams the rows [r0, r1) of a workgroup: wave w starts with row r0 + w, so
+// the waves of a CU stream neighbouring rows (rows a power of two apart share
+// memory channels) and few rows spread over its SIMDs; then each takes the
+// next.
+template <class Vec, int U, int NW>
+__device__ __forceinline__ void rows_stream(const typename Vec::Mem* __restrict__ logits, int nvec,
+                                            const RowsChunk* chunk, int nc, int r0, int r1, int* s_next,
+                                            typename Vec::Raw* s_kept, const RowOut& out) {
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  int r = r0 + wave;
+  if (r >= r1) return;
+  int k = rows_search(chunk, nc, r);
+  for (;;) {
+    while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
+    k = __builtin_amdgcn_readfirstlane(k);
+    const int slot = rows_slot(chunk[k], r);
+    const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, 0,
+                                               s_kept + wave * U * kWave, s_kept + NW * U * kWave);
+    const RowResult rr = finish_row_x(wp.m, wp.K, wp.S, wp.first);
+    if (lane == 0) store_row(out, (size_t)slot, rr);
+    int next = 0;
+    if (lane == 0) next = atomicAdd(s_next, 1);
+    r = r0 + NW + __builtin_amdgcn_readfirstlane(next);
+    if (r >= r1) return;
+  }
+}
+
+// The rows of the windows win(j) of sequences seq(j), split over S waves and shared evenly
+// by `groups` workgroups of NW waves: workgroup g takes every groups-th row, its NW / S teams in turn, every wave
+// its part of a row, and the last wave of a team to finish a row combines the
+// parts, as the row groups of k_confidence would (the same bits); the others
+// are at the team's next row by then.  A team's parts wait in a ring of
+// kRowsRing rows.  (Contiguous shares take the same time on buffers in use,
+// but the first pass over new ones waits for each CU's own pages: 100 blocks
+// of 8..48, float32, V = 126464 236 against 234 us, new buffers 326 against
+// 297.)
+constexpr int kRowsRing = 8;
+
+template <int NW, int S>
+struct RowsRing {
+  static constexpr int kTeams = NW / S;
+  WavePartial part[kRowsRing][NW];
+  int arrived[kRowsRing][kTeams];    // waves done with the ring's rows
+  int combined[kTeams];              // rows a team has combined
+  int wave_n[NW];                    // rows_find
+};
+
+template <class Vec, int U, int S, int NW, class Seq, class Win>
+__device__ __forceinline__ void rows_split(const typename Vec::Mem* __restrict__ logits, int n_seq, Seq&& seq,
+                                           Win&& win, int L, int C, int nvec,
+                                           const uint8_t* __restrict__ mask, int slots, const RowOut& out,
+                                           int group, int groups, RowsChunk* chunk, RowsRing<NW, S>& ring,
+                                           typename Vec::Raw* s_kept) {
+  constexpr int kTeams = NW / S;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int team = wave / S, w = wave % S;
+  for (int i = threadIdx.x; i < kRowsRing * kTeams; i += NW * kWave) ring.arrived[i / kTeams][i % kTeams] = 0;
+  if (threadIdx.x < kTeams) ring.combined[threadIdx.x] = 0;
+  const int total = rows_find<NW>(chunk, ring.wave_n, n_seq, win, C, mask, slots);
+  rows_defaults<NW>(chunk, n_seq, seq, L, C, (unsigned)group, (unsigned)groups, out);
+  if constexpr (S == 1) {
+    const int r0 = __builtin_amdgcn_readfirstlane((int)((long long)group * total / groups));
+    const int r1 = __builtin_amdgcn_readfirstlane((int)((long long)(group + 1) * total / groups));
+    rows_stream<Vec, U, NW>(logits, nvec, chunk, n_seq * C, r0, r1, &ring.combined[0], s_kept, out);
+    return;
+  }
+  for (int step = 0;; ++step) {
+    const int r = (step * kTeams + team) * groups + group;
+    if (r >= total) return;
+    const int k = rows_search(chunk, n_seq * C, r);
+    const int slot = rows_slot(chunk[k], r);
+    const WavePartial wp = row_pass<Vec, U, S>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, w,
+                                               s_kept + wave * U * kWave, s_kept + NW * U * kWave);
+    const int at = step % kRowsRing;
+    // the ring's place is free once its row before has been combined; that
+    // waits for no later row, so the wait ends
+    if (step >= kRowsRing)
+      while (__hip_atomic_load(&ring.combined[team], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <=
+             step - kRowsRing)
+        __builtin_amdgcn_s_sleep(1);
+    if (lane == 0) ring.part[at][wave] = wp;
+    __threadfence_block();
+    int before = 0;
+    if (lane == 0) before = atomicAdd(&ring.arrived[at][team], 1);
+    if (__builtin_amdgcn_readfirstlane(before) != S - 1) continue;
+    __threadfence_block();
+    const WavePartial mine = lane < S ? ring.part[at][team * S + lane]
+                                      : WavePartial{kNegInf, kRefFloor, 0.0, 0x7fffffff};
+    const RowResult rr = combine_parts_lanes<S>(mine);
+    if (lane == 0) {
+      store_row(out, (size_t)slot, rr);
+      ring.arrived[at][team] = 0;
+      __hip_atomic_store(&ring.combined[team], step + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+}
+
 // Row group r of the grid handles the window-relative slot (b, q), q < W =
 // row_groups(B, L): the window positions q, q + W, ... of sequence b (one for a
 // window of at most W positions), and the defaults of the positions j = q,
 // q + W, ... of the whole row of L slots that lie outside the window.  So
 // only B W row groups are launched, however long the span L.
-template <class Vec, int U, int S>
+//
+// A row group is launched whether or not its positions are masked: the best
+// grid for windows of at most W, whatever the span.  The positions beyond W of
+// a longer window would take second turns in some row groups.  So with kLong
+// (spans that can hold one: at most kLongMaxB sequences, W = 32, B L < 2^31)
+// the row groups of longer windows share the candidate rows of all such
+// windows evenly, by number (rows_split), with the same bits; the first
+// `groups` of their workgroups, as many as the chip holds, do the work.  The
+// windows decide, not the span, and a workgroup of a short window looks at no
+// other sequence's: reading all bounds first costs every workgroup a round
+// trip (64 blocks of 1..32 in spans of 512 66.7 -> 68.3 us).  At V = 126464
+// 100 full blocks of 48 227 -> 203 us, 24 in spans of 96 86 -> 72, 16 of 100
+// in spans of 800 118 -> 104; 48 blocks of 5..40 in spans of 200 at V = 50257
+// 62 -> 39, 100 of 5..40 in spans of 320 at V = 32000 59 -> 41.  Blocks of 32
+// are best in their row groups: sharing their rows took 64 full blocks in
+// spans of 293 from 95 to 107 us, 200 in spans of 100 at V = 32000 84 to 98.
+constexpr int kLongMaxB = 255;
+constexpr int kLongChunks = 1024;       // LDS room; more chunks: row groups
+
+// The sequences with windows longer than W, by a workgroup of NW waves.
+struct LongSeqs {
+  static constexpr int kWords = (kLongMaxB + kWave - 1) / kWave;
+  unsigned long long word[kWords];     // a bit a sequence
+  int longest[kWords];
+  unsigned char seq[kWords * kWave];   // their numbers and windows
+  RowsWindow win[kWords * kWave];
+};
+
+template <class Vec, int U, int S, bool kLong>
 __global__ void __launch_bounds__(SplitShape<S>::kThreads)
 k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
              const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
-             const int32_t* __restrict__ bend, RowOut out) {
+             const int32_t* __restrict__ bend, RowOut out, int groups) {
   using Shape = SplitShape<S>;
   __shared__ WavePartial part[Shape::kWaves];
   __shared__ typename Vec::Raw s_kept[U * (Shape::kThreads + kWave)];
@@ -492,6 +753,62 @@ k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nve
     }
   }
   const size_t row0 = (size_t)b * L;
+  if constexpr (kLong) {
+    if (len > W) {                      // the workgroup's row groups are of one sequence
+      __shared__ RowsChunk s_chunk[kLongChunks];
+      __shared__ RowsRing<Shape::kWaves, S> s_ring;
+      __shared__ LongSeqs s_long;
+      static_assert(Shape::kWaves >= LongSeqs::kWords, "a wave a word");
+      const int at = wave * kWave + lane;
+      bool is_long = false;
+      int n = 0, s1 = 0;
+      if (wave < LongSeqs::kWords) {
+        if (at < B) {
+          s1 = bstart[at];
+          const int e1 = bend[at];
+          if (window_ok(s1, e1, L)) n = e1 - s1;
+        }
+        is_long = n > W;
+        const unsigned long long word = __ballot(is_long);
+        const int longest = -wave_min(-n);
+        if (lane == 0) {
+          s_long.word[wave] = word;
+          s_long.longest[wave] = longest;
+        }
+      }
+      __syncthreads();
+      int n_long = 0, longest = 0, own = 0, mine = 0;   // before sequence b, before sequence `at`
+  #pragma unroll
+      for (int i = 0; i < LongSeqs::kWords; ++i) {
+        const unsigned long long word = s_long.word[i];
+        auto below = [&](int seq) {
+          const int bits = seq - i * kWave;
+          return __popcll(bits <= 0 ? 0ull : bits >= kWave ? word : word & ((1ull << bits) - 1ull));
+        };
+        own += below(b);
+        mine += below(at);
+        n_long += __popcll(word);
+        longest = max(longest, s_long.longest[i]);
+      }
+      const int C = (longest + kWave - 1) / kWave;
+      if (n_long * C <= kLongChunks) {
+        constexpr int kPer = 32 / Shape::kRows;  // workgroups a sequence
+        const int group = own * kPer + (int)(blockIdx.x % kPer);
+        const int n_groups = min(groups, n_long * kPer);
+        if (group >= n_groups) return;
+        if (is_long) {
+          s_long.seq[mine] = (unsigned char)at;
+          s_long.win[mine] = RowsWindow{at * L + s1, n};
+        }
+        __syncthreads();
+        rows_split<Vec, U, S, Shape::kWaves>(
+            logits, __builtin_amdgcn_readfirstlane(n_long), [&](int j) { return (int)s_long.seq[j]; },
+            [&](int j) { return s_long.win[j]; }, L, __builtin_amdgcn_readfirstlane(C), nvec, mask, B * L, out, __builtin_amdgcn_readfirstlane(group),
+            __builtin_amdgcn_readfirstlane(n_groups), s_chunk, s_ring, s_kept);
+        return;
+      }
+    }
+  }
   // defaults of this row group's positions outside the window, one per lane
   if (live && w == 0)
     for (int j = q + lane * W; j < L; j += W * kWave)
@@ -1142,8 +1459,7 @@ k_fused_wide(const typename Vec::Mem* __restrict__ logits, int B, int L, int nve
 // takes as long as the CU whose sequences have the most candidates: a wave
 // takes a row of V = 126464 in 37 us of arithmetic, alone or beside three
 // others, and the waves of another CU cannot help.  Here one workgroup of
-// kRowsWaves waves per CU finds every sequence's candidates (64 positions a
-// ballot; the words, their running counts and first slots in LDS), and
+// kRowsWaves waves per CU finds every sequence's candidates (rows_find), and
 // workgroup g of n takes the rows [g T / n, (g + 1) T / n) of all T, each as
 // k_fused would, with the same bits.  The selection follows as a launch of
 // its own.  Which batches take it: make_plan.
@@ -1151,143 +1467,8 @@ constexpr int kRowsWaves = 16;
 constexpr int kRowsThreads = kRowsWaves * kWave;
 constexpr size_t kRowsLds = 160 * 1024;
 
-struct RowsChunk {
-  unsigned long long word;   // candidates among 64 window positions
-  int first;                 // slot of the first of them
-  int before;                // candidates of all chunks before
-  int len;                   // positions
-};
-
-// 64-position chunks of a sequence's window at most
-__host__ __device__ inline int rows_chunks(int L) { return ((L < kMaxBlock ? L : kMaxBlock) + kWave - 1) / kWave; }
 template <class Vec, int U>
 constexpr size_t rows_kept_bytes() { return (size_t)U * (kRowsWaves + 1) * kWave * sizeof(typename Vec::Raw); }
-
-// Every chunk's candidates and their running counts, by the whole workgroup;
-// returns the number of candidates.  Three round trips to memory and LDS in
-// all, whatever B: the bounds, the mask bytes (kRowsBatch chunks a wave in
-// flight), the counts.
-__device__ __forceinline__ int rows_find(RowsChunk* chunk, int* s_wave, int B, int L,
-                                         const uint8_t* __restrict__ mask,
-                                         const int32_t* __restrict__ bstart,
-                                         const int32_t* __restrict__ bend) {
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int C = rows_chunks(L), nc = B * C;
-  for (int k = tid; k < nc; k += kRowsThreads) {
-    const int b = (int)((unsigned)k / (unsigned)C), c = k - b * C;
-    const int s = bstart[b], e = bend[b];
-    const int n = window_ok(s, e, L) ? max(0, min(e - s - c * kWave, kWave)) : 0;
-    chunk[k].len = n;
-    chunk[k].first = n > 0 ? b * L + s + c * kWave : 0;
-  }
-  __syncthreads();
-  constexpr int kRowsBatch = 16;
-  for (int k0 = wave; k0 < nc; k0 += kRowsWaves * kRowsBatch) {
-    uint8_t m[kRowsBatch];
-#pragma unroll
-    for (int i = 0; i < kRowsBatch; ++i) {
-      const int k = k0 + i * kRowsWaves;
-      const bool in = k < nc && lane < chunk[k < nc ? k : 0].len;
-      m[i] = mask[in ? chunk[k < nc ? k : 0].first + lane : 0];     // past the chunk: slot 0, not used
-    }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < kRowsBatch; ++i) {
-      const int k = k0 + i * kRowsWaves;
-      if (k >= nc) break;
-      const unsigned long long w = __ballot(lane < chunk[k].len && m[i] != 0);
-      if (lane == 0) chunk[k].word = w;
-    }
-  }
-  __syncthreads();
-  // running counts: thread t takes the chunks [t per, (t + 1) per)
-  const int per = (nc + kRowsThreads - 1) / kRowsThreads;
-  int own = 0;
-  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) own += __popcll(chunk[k].word);
-  int incl = own;
-#pragma unroll
-  for (int x = 1; x < kWave; x <<= 1) {
-    const int o = __shfl_up(incl, x);
-    if (lane >= x) incl += o;
-  }
-  if (lane == kWave - 1) s_wave[wave] = incl;
-  __syncthreads();
-  int run = incl - own, total = 0;
-#pragma unroll
-  for (int w = 0; w < kRowsWaves; ++w) {
-    if (w < wave) run += s_wave[w];
-    total += s_wave[w];
-  }
-  for (int k = tid * per; k < min(nc, (tid + 1) * per); ++k) {
-    chunk[k].before = run;
-    run += __popcll(chunk[k].word);
-  }
-  __syncthreads();
-  return total;
-}
-
-// The default outputs of the non-candidates, shared by all workgroups.  The
-// positions are unsigned: a stride past the last of them (at most 2^31 - 1)
-// still fits.
-__device__ __forceinline__ void rows_defaults(const RowsChunk* chunk, int B, int L, const RowOut& out) {
-  const int C = rows_chunks(L);
-  const unsigned slots = (unsigned)B * (unsigned)L;
-  for (unsigned p = blockIdx.x * kRowsThreads + threadIdx.x; p < slots; p += gridDim.x * kRowsThreads) {
-    const int b = (int)(p / (unsigned)L);
-    const int first = chunk[b * C].first;      // of the window; an empty one has no candidates
-    const int rel = (int)p - first;
-    const bool in = rel >= 0 && rel < C * kWave && first >= b * L;
-    const unsigned long long word = in ? chunk[b * C + rel / kWave].word : 0ull;
-    if (((word >> (rel % kWave)) & 1ull) == 0ull) store_default(out, (size_t)p);
-  }
-}
-
-// The last chunk of [0, nc) with before <= r.
-__device__ __forceinline__ int rows_search(const RowsChunk* chunk, int nc, int r) {
-  int lo = 0, hi = nc - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) / 2;
-    if (chunk[mid].before <= r) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// The slot of row r: the (r - before)-th candidate of its chunk.
-__device__ __forceinline__ int rows_slot(const RowsChunk& c, int r) {
-  const int lane = threadIdx.x % kWave;
-  const int rank = __popcll(c.word & ((1ull << lane) - 1ull));
-  const int pos = (int)__builtin_ctzll(__ballot(((c.word >> lane) & 1ull) && rank == r - c.before));
-  return __builtin_amdgcn_readfirstlane(c.first + pos);
-}
-
-// Streams the rows [r0, r1) of a workgroup: wave w starts with row r0 + w, so
-// the waves of a CU stream neighbouring rows (rows a power of two apart share
-// memory channels) and few rows spread over its SIMDs; then each takes the
-// next.  `done(k, r, slot, result)` per row, k its chunk.
-template <class Vec, int U, class F>
-__device__ __forceinline__ void rows_stream(const typename Vec::Mem* __restrict__ logits, int nvec,
-                                            const RowsChunk* chunk, int nc, int r0, int r1, int* s_next,
-                                            typename Vec::Raw* s_kept, F&& done) {
-  const int lane = threadIdx.x % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  int r = r0 + wave;
-  if (r >= r1) return;
-  int k = rows_search(chunk, nc, r);
-  for (;;) {
-    while (k + 1 < nc && chunk[k + 1].before <= r) ++k;
-    k = __builtin_amdgcn_readfirstlane(k);
-    const int slot = rows_slot(chunk[k], r);
-    const WavePartial wp = row_pass<Vec, U, 1>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, 0,
-                                               s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
-    done(k, r, slot, finish_row_x(wp.m, wp.K, wp.S, wp.first));
-    int next = 0;
-    if (lane == 0) next = atomicAdd(s_next, 1);
-    r = r0 + kRowsWaves + __builtin_amdgcn_readfirstlane(next);
-    if (r >= r1) return;
-  }
-}
 
 template <class Vec, int U>
 __global__ void __launch_bounds__(kRowsThreads)
@@ -1300,79 +1481,17 @@ k_rows(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
   __shared__ int s_wave[kRowsWaves];
   __shared__ int s_next;
   if (threadIdx.x == 0) s_next = 0;
-  const int total = rows_find(chunk, s_wave, B, L, mask, bstart, bend);
-  rows_defaults(chunk, B, L, out);
+  const int C = rows_chunks(L);
+  auto all = [](int j) { return j; };
+  auto win = [&](int j) {
+    const int s = bstart[j], e = bend[j];
+    return window_ok(s, e, L) ? RowsWindow{j * L + s, e - s} : RowsWindow{0, 0};
+  };
+  const int total = rows_find<kRowsWaves>(chunk, s_wave, B, win, C, mask, B * L);
+  rows_defaults<kRowsWaves>(chunk, B, all, L, C, blockIdx.x, gridDim.x, out);
   const int r0 = __builtin_amdgcn_readfirstlane((int)((long long)blockIdx.x * total / gridDim.x));
   const int r1 = __builtin_amdgcn_readfirstlane((int)((long long)(blockIdx.x + 1) * total / gridDim.x));
-  rows_stream<Vec, U>(logits, nvec, chunk, B * rows_chunks(L), r0, r1, &s_next, s_kept,
-                      [&](int, int, int slot, const RowResult& rr) {
-                        if (threadIdx.x % kWave == 0) store_row(out, (size_t)slot, rr);
-                      });
-}
-
-// The same for rows split over S waves: workgroup g of n takes every n-th row,
-// its kRowsWaves / S teams in turn, every wave its part of a row, and the last wave of a team
-// to finish a row combines the parts, as k_confidence would (the same bits);
-// the others are at the team's next row by then.  A team's parts wait in a
-// ring of kRowsRing rows.
-constexpr int kRowsRing = 8;
-
-template <class Vec, int U, int S>
-__global__ void __launch_bounds__(kRowsThreads)
-k_rows_split(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
-             const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
-             const int32_t* __restrict__ bend, RowOut out) {
-  constexpr int kTeams = kRowsWaves / S;
-  extern __shared__ __attribute__((aligned(16))) char rows_lds[];
-  typename Vec::Raw* s_kept = reinterpret_cast<typename Vec::Raw*>(rows_lds);
-  RowsChunk* chunk = reinterpret_cast<RowsChunk*>(rows_lds + rows_kept_bytes<Vec, U>());
-  __shared__ int s_wave[kRowsWaves];
-  __shared__ WavePartial ring[kRowsRing][kRowsWaves];
-  __shared__ int arrived[kRowsRing][kTeams];    // waves done with the ring's rows
-  __shared__ int combined[kTeams];              // rows a team has combined
-  const int lane = threadIdx.x % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  const int team = wave / S, w = wave % S;
-  for (int i = threadIdx.x; i < kRowsRing * kTeams; i += kRowsThreads) arrived[i / kTeams][i % kTeams] = 0;
-  if (threadIdx.x < kTeams) combined[threadIdx.x] = 0;
-  const int total = rows_find(chunk, s_wave, B, L, mask, bstart, bend);
-  rows_defaults(chunk, B, L, out);
-  const int nc = B * rows_chunks(L);
-  for (int step = 0;; ++step) {
-    // every (workgroups)-th row, the workgroup's teams in turn: the chip moves
-    // through the rows as one front.  A contiguous share per workgroup takes
-    // the same time on buffers in use, but the first pass over new ones waits
-    // for each CU's own pages: 100 blocks of 8..48, float32, V = 126464 236
-    // against 234 us, new buffers 326 against 297.  (k_rows keeps contiguous
-    // shares: 300 blocks of 32..128 281 against 295 us, new buffers 376 against
-    // 356; 456 before either.)
-    const int r = (step * kTeams + team) * (int)gridDim.x + (int)blockIdx.x;
-    if (r >= total) return;
-    const int k = __builtin_amdgcn_readfirstlane(rows_search(chunk, nc, r));
-    const int slot = rows_slot(chunk[k], r);
-    const WavePartial wp = row_pass<Vec, U, S>(row_at<Vec>(logits, (size_t)slot, nvec), nvec, w,
-                                               s_kept + wave * U * kWave, s_kept + kRowsWaves * U * kWave);
-    const int at = step % kRowsRing;
-    // the ring's place is free once its row before has been combined; that
-    // waits for no later row, so the wait ends
-    if (step >= kRowsRing)
-      while (__hip_atomic_load(&combined[team], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= step - kRowsRing)
-        __builtin_amdgcn_s_sleep(1);
-    if (lane == 0) ring[at][wave] = wp;
-    __threadfence_block();
-    int before = 0;
-    if (lane == 0) before = atomicAdd(&arrived[at][team], 1);
-    if (__builtin_amdgcn_readfirstlane(before) != S - 1) continue;
-    __threadfence_block();
-    const WavePartial mine = lane < S ? ring[at][team * S + lane]
-                                      : WavePartial{kNegInf, kRefFloor, 0.0, 0x7fffffff};
-    const RowResult rr = combine_parts_lanes<S>(mine);
-    if (lane == 0) {
-      store_row(out, (size_t)slot, rr);
-      arrived[at][team] = 0;
-      __hip_atomic_store(&combined[team], step + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-  }
+  rows_stream<Vec, U, kRowsWaves>(logits, nvec, chunk, B * C, r0, r1, &s_next, s_kept, out);
 }
 
 __global__ void __launch_bounds__(256) k_reveal(const uint8_t* __restrict__ commit,
@@ -1433,8 +1552,10 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Mem* __restri
 // ---------------------------------------------------------------------------
 struct Plan {
   bool fused;   // one workgroup per sequence, selection in the same kernel
-  bool rows;    // where they fit (and, fused, where the outputs have a place): evenly
-                // shared rows, then the selection
+  bool rows;    // fused, where they fit and the outputs have a place: evenly shared rows,
+                // then the selection
+  bool lengths; // not fused: evenly shared rows where a window is longer than the row
+                // groups (decided on the device)
   int split;    // wavefronts per row in the confidence kernel
   int parts;    // decode step with a workspace: split over split / 4 workgroups (0: no)
   int rem;      // fused: the last rem sequences take the small-batch plan, beside (0: none)
@@ -1503,18 +1624,11 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
     // a row split 8 or 16 ways fills one CU; blocks of at most one wavefront
     // can take their rows' parts from several workgroups instead
     if (L <= kWaveBlock && p.split >= 8) p.parts = p.split;
-    // A row group is a window position (and those 32 further on), launched
-    // whether or not it is masked: the best grid for blocks of 32, whatever
-    // the span.  A span that is no multiple of 32 holds other blocks, whose
-    // positions beyond 32 take second turns in some row groups; their rows are
-    // shared evenly instead (the search costs about 5 us): at V = 126464 100
-    // full blocks of 48 222 -> 201 us and 24 full blocks of 48 in spans of 96
-    // 86 -> 72, 48 blocks of 5..40 in spans of 200 at V = 50257 59 -> 39, 16
-    // blocks of 1..100 in spans of 200 at V = 4000 34 -> 23.  Blocks of 32 lose
-    // with all positions masked (64 x 32 95 -> 101, 128 x 32 171 -> 183) and gain
-    // with few (192 with 1..4 52 -> 35); parts from several workgroups are
-    // better than either (40 full blocks of 40 82 against 97).
-    p.rows = B >= kGroups32MinB && L > 32 && L % 32 != 0 && !p.parts;
+    // spans that can hold a window longer than the row groups: see
+    // k_confidence.  Parts from several workgroups are better than either
+    // (40 full blocks of 40 82 against 97 us).
+    p.lengths = B >= kGroups32MinB && B <= kLongMaxB && L > row_groups(B, L) && !p.parts &&
+                (long long)B * L <= 0x7fffffffLL;
   }
   return p;
 }
@@ -1527,16 +1641,22 @@ static bool vec_path(const void* logits, int V, fdllm_dtype dt) {
 template <class Vec>
 static hipError_t launch_confidence_t(const void* logits, int B, int L, int nvec, int split,
                                       const uint8_t* mask, const int32_t* bs, const int32_t* be,
-                                      RowOut out, hipStream_t st) {
+                                      RowOut out, bool lengths, hipStream_t st) {
   const long long nvslots = (long long)B * row_groups(B, L);   // window-relative
+  const int cus = lengths ? device_cus() : 0;
   const auto* lg = (const typename Vec::Mem*)logits;
 #define FDLLM_CONF_CASE(SPLIT)                                                                  \
   case SPLIT: {                                                                                 \
     using Sh = SplitShape<SPLIT>;                                                               \
-    const long long grid = (nvslots + Sh::kRows - 1) / Sh::kRows;                               \
-    hipLaunchKernelGGL((k_confidence<Vec, SPLIT == 1 ? Vec::kU : Vec::kUSplit, SPLIT>),           \
-                       dim3((unsigned)grid), dim3(Sh::kThreads),                                \
-                       0, st, lg, B, L, nvec, mask, bs, be, out);                               \
+    constexpr int U = SPLIT == 1 ? Vec::kU : Vec::kUSplit;                                      \
+    const dim3 grid((unsigned)((nvslots + Sh::kRows - 1) / Sh::kRows)), block(Sh::kThreads);    \
+    const int groups = cus * (kRowsWaves / Sh::kWaves);   /* 16 waves a CU */                   \
+    if (groups > 0)                                                                             \
+      hipLaunchKernelGGL((k_confidence<Vec, U, SPLIT, true>), grid, block, 0, st, lg, B, L,     \
+                         nvec, mask, bs, be, out, groups);                                      \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_confidence<Vec, U, SPLIT, false>), grid, block, 0, st, lg, B, L,    \
+                         nvec, mask, bs, be, out, 0);                                           \
     break;                                                                                      \
   }
   switch (split) {
@@ -1589,15 +1709,15 @@ static hipError_t launch_confidence_parts(const void* logits, fdllm_dtype dt, in
 
 static hipError_t launch_confidence(const void* logits, fdllm_dtype dt, int B, int L, int V,
                                     int split, const uint8_t* mask, const int32_t* bs,
-                                    const int32_t* be, RowOut out, hipStream_t st) {
+                                    const int32_t* be, RowOut out, bool lengths, hipStream_t st) {
   if (vec_path(logits, V, dt)) {
     if (dt == FDLLM_BF16)
-      return launch_confidence_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, st);
-    return launch_confidence_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, st);
+      return launch_confidence_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, lengths, st);
+    return launch_confidence_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, lengths, st);
   }
   if (dt == FDLLM_BF16)
-    return launch_confidence_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, st);
-  return launch_confidence_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, st);
+    return launch_confidence_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, lengths, st);
+  return launch_confidence_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, lengths, st);
 }
 
 template <int R, bool Robust>
@@ -1633,9 +1753,9 @@ hipError_t launch_select(fdllm_selector sel, const SelectIO& io, int B, int L, f
   return launch_select(sel, io, B, L, param, st, 0, nullptr, RowOut{});
 }
 
-// The kernels over evenly shared rows: whether their LDS holds the batch, and
-// the launches (one workgroup per CU, all resident).
-static constexpr size_t kRowsLdsMax = kRowsLds - 4096;   // less the kernels' static part
+// The kernel over evenly shared whole rows (Plan::rows): whether its LDS holds
+// the batch, and the launch (one workgroup per CU).
+static constexpr size_t kRowsLdsMax = kRowsLds - 4096;   // less the kernel's static part
 
 template <class Vec>
 static bool rows_fit(int B, int L) {
@@ -1644,61 +1764,42 @@ static bool rows_fit(int B, int L) {
          nc * (long long)sizeof(RowsChunk) + (long long)rows_kept_bytes<Vec, Vec::kU>() <= (long long)kRowsLdsMax;
 }
 
-// S = 1: k_rows.  The LDS limit is raised once per device, before the first
-// launch there.
-template <class Vec, int S>
-static hipError_t launch_rows_s(const void* logits, int B, int L, int nvec, const uint8_t* mask,
+// The LDS limit is raised once per device, before the first launch there.
+template <class Vec>
+static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, const uint8_t* mask,
                                 const int32_t* bs, const int32_t* be, RowOut out, hipStream_t st) {
-  constexpr int U = S == 1 ? Vec::kU : Vec::kUSplit;
+  constexpr int U = Vec::kU;
   static std::atomic<bool> allowed[64];
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  auto kernel = [] {
-    if constexpr (S == 1) return k_rows<Vec, U>;
-    else return k_rows_split<Vec, U, S>;
-  }();
   if (!allowed[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowsLdsMax);
+    e = hipFuncSetAttribute((const void*)k_rows<Vec, U>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kRowsLdsMax);
     if (e != hipSuccess) return e;
     allowed[dev].store(true, std::memory_order_release);
   }
   const size_t lds = rows_kept_bytes<Vec, U>() + (size_t)B * rows_chunks(L) * sizeof(RowsChunk);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
+  hipLaunchKernelGGL((k_rows<Vec, U>), dim3((unsigned)device_cus()), dim3(kRowsThreads), lds, st,
                      (const typename Vec::Mem*)logits, B, L, nvec, mask, bs, be, out);
   return hipGetLastError();
 }
-template <class Vec>
-static hipError_t launch_rows_t(const void* logits, int B, int L, int nvec, int split,
-                                const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
-                                hipStream_t st) {
-  switch (split) {
-    case 1: return launch_rows_s<Vec, 1>(logits, B, L, nvec, mask, bs, be, out, st);
-    case 2: return launch_rows_s<Vec, 2>(logits, B, L, nvec, mask, bs, be, out, st);
-    case 4: return launch_rows_s<Vec, 4>(logits, B, L, nvec, mask, bs, be, out, st);
-    case 8: return launch_rows_s<Vec, 8>(logits, B, L, nvec, mask, bs, be, out, st);
-    case 16: return launch_rows_s<Vec, 16>(logits, B, L, nvec, mask, bs, be, out, st);
-    default: return hipErrorInvalidValue;
-  }
-}
 
-// The vocabulary pass of a rows plan (Plan::rows): whether it can run here,
-// and the launch.
 static bool rows_ok(const void* logits, fdllm_dtype dt, int B, int L, int V) {
   if (device_cus() < 1) return false;
   if (vec_path(logits, V, dt)) return dt == FDLLM_BF16 ? rows_fit<VecBf16x8>(B, L) : rows_fit<VecF32x4>(B, L);
   return dt == FDLLM_BF16 ? rows_fit<VecBf16Any>(B, L) : rows_fit<VecF32Any>(B, L);
 }
-static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V, int split,
+static hipError_t launch_rows(const void* logits, fdllm_dtype dt, int B, int L, int V,
                               const uint8_t* mask, const int32_t* bs, const int32_t* be, RowOut out,
                               hipStream_t st) {
   if (vec_path(logits, V, dt)) {
-    if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, st);
-    return launch_rows_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, st);
+    if (dt == FDLLM_BF16) return launch_rows_t<VecBf16x8>(logits, B, L, V / 8, mask, bs, be, out, st);
+    return launch_rows_t<VecF32x4>(logits, B, L, V / 4, mask, bs, be, out, st);
   }
-  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, st);
-  return launch_rows_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, st);
+  if (dt == FDLLM_BF16) return launch_rows_t<VecBf16Any>(logits, B, L, V, mask, bs, be, out, st);
+  return launch_rows_t<VecF32Any>(logits, B, L, V, mask, bs, be, out, st);
 }
 
 template <class Vec, int R, bool Robust>
@@ -1833,11 +1934,6 @@ static fdllm_status step_split(const Plan& p, fdllm_selector sel, const void* lo
   const RowOut out{tokens, conf, eps, lse};
   SelectIO io{conf, eps, mask, block_start, block_end, commit, n_commit, tokens, x, etain};
   hipError_t err;
-  if (p.rows && rows_ok(logits, dtype, B, L, V)) {
-    err = launch_rows(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, st);
-    if (err != hipSuccess) return FDLLM_ERR_HIP;
-    return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
-  }
   if (p.parts && workspace && workspace_bytes >= out_bytes_for(B, L) +
                                                      align256(n * p.parts * sizeof(WavePartial))) {
     // the rows' parts from several workgroups each, combined by the selection
@@ -1849,7 +1945,7 @@ static fdllm_status step_split(const Plan& p, fdllm_selector sel, const void* lo
     err = launch_select(sel, io, B, L, param, st, p.parts, parts, out);
     return err == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
   }
-  err = launch_confidence(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, st);
+  err = launch_confidence(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, p.lengths, st);
   if (err != hipSuccess) return FDLLM_ERR_HIP;
   err = launch_select(sel, io, B, L, param, st);
   return err == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
@@ -1937,21 +2033,22 @@ fdllm_status fdllm_confidence(const void* logits, fdllm_dtype dtype, int B, int 
   RowOut out{tokens, conf, eps, lse};
   hipStream_t st = (hipStream_t)stream;
   if (p.rows && rows_ok(logits, dtype, B, L, V))
-    return launch_rows(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, st) == hipSuccess
+    return launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, out, st) == hipSuccess
                ? FDLLM_OK
                : FDLLM_ERR_HIP;
   // the rows of a fused step's small-batch remainder are split as the decode
   // step splits them, so that both give the same bits
   const int b0 = B - p.rem;
   hipError_t err = launch_confidence(logits, dtype, b0, L, V, p.split, mask, block_start, block_end,
-                                     out, st);
+                                     out, p.lengths, st);
   if (err == hipSuccess && p.rem) {
     const size_t r0 = (size_t)b0 * (size_t)L;
     const size_t esize = dtype == FDLLM_BF16 ? 2 : 4;
     auto off = [](auto* ptr, size_t k) { return ptr ? ptr + k : ptr; };
     err = launch_confidence((const char*)logits + r0 * (size_t)V * esize, dtype, p.rem, L, V,
                             p.rsplit, mask + r0, block_start + b0, block_end + b0,
-                            RowOut{off(tokens, r0), off(conf, r0), off(eps, r0), off(lse, r0)}, st);
+                            RowOut{off(tokens, r0), off(conf, r0), off(eps, r0), off(lse, r0)}, false,
+                            st);
   }
   return err == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
 }
@@ -2059,7 +2156,7 @@ fdllm_status decode_step(const void* logits, fdllm_dtype dtype, int B, int L, in
     char* ws = (char*)workspace;
     const RowOut o{tokens ? tokens : (int32_t*)ws, conf ? conf : (float*)(ws + n),
                    eps ? eps : (float*)(ws + 2 * n), lse};
-    if (launch_rows(logits, dtype, B, L, V, 1, mask, block_start, block_end, o, st) != hipSuccess)
+    if (launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, o, st) != hipSuccess)
       return FDLLM_ERR_HIP;
     const SelectIO io{o.conf, o.eps, mask, block_start, block_end, commit, n_commit, o.tokens, x, etain};
     return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;

@@ -584,8 +584,8 @@ def test_rows_of_any_length_and_start(gpu, V, dt):
     (9, 70, 17000, torch.bfloat16, 3),         # fewer rows than workgroups
 ])
 def test_shared_split_rows(gpu, B, L, V, dt, window):
-    """Split rows shared evenly by the workgroups' teams: the oracle's rows and
-    decisions, fdllm_confidence's bits in the decode step, and equal rows equal
+    """Rows of windows longer than 32, shared evenly by the workgroups' teams: the
+    oracle's rows and decisions, fdllm_confidence's bits in the decode step, and equal rows equal
     bits; the last sequence has no candidate, the first an invalid window."""
     inp = workloads.random_case(B, L, V, dt, device="cuda", seed=B + L, window=window, poison=False)
     inp.start[0], inp.end[0] = 5, 3
@@ -636,3 +636,58 @@ def test_shared_rows_longest_span(gpu):
     want[B - 1, L - 1] = 0
     assert torch.equal(tokens, want)
     assert bool((buf[B * L:] == -7).all())
+
+
+@pytest.mark.parametrize("B,L,V,dt", [
+    (8, 100, 126464, torch.bfloat16),          # rows split 16 ways
+    (48, 200, 50257, torch.bfloat16),          # 8 ways, odd rows
+    (12, 1024, 20000, torch.float32),          # windows of up to 16 chunks
+    (128, 96, 70000, torch.bfloat16),          # 4 ways
+    (200, 64, 40000, torch.float32),           # 2 ways
+    (255, 65, 3000, torch.bfloat16),           # whole rows, as many sequences as take this path
+    (64, 1024, 300, torch.bfloat16),           # as many chunks as fit, or more
+    (200, 1024, 64, torch.float32),            # more: row groups
+    (300, 130, 200, torch.bfloat16),           # a large batch: the rows of all sequences
+])
+def test_long_windows_equal_their_pieces(gpu, B, L, V, dt):
+    """Windows of every kind side by side (empty, short, 32, 33, several
+    wavefronts, invalid, up to the last position), masks of any non-zero byte:
+    the candidates' bits are those of the same windows taken in pieces of at
+    most 32 positions, each of which has row groups of its own."""
+    say(f"[long windows] B={B} L={L} V={V} {dt}")
+    g = torch.Generator().manual_seed(B + L + V)
+    logits = torch.randn((B, L, V), generator=g).to(dt).cuda()
+    lens = torch.tensor([0, 1, 31, 32, 33, 40, 63, 64, 65, 100, 640, 1024]).clamp(max=L)
+    n = lens[torch.randint(0, len(lens), (B,), generator=g)]
+    start = (torch.rand(B, generator=g) * (L - n + 1)).to(torch.int32)
+    n[B - 1] = min(L, 77)
+    start[B - 1] = L - int(n[B - 1])                        # to the end of the mask array
+    end = start + n.to(torch.int32)
+    start[1], end[1] = -1, 40                               # invalid
+    start[5], end[5] = 2, L + 1                             # invalid
+    byte = torch.tensor([0, 0, 1, 2, 127, 128, 255], dtype=torch.uint8)
+    mask = byte[torch.randint(0, 7, (B, L), generator=g)].cuda()
+
+    def run(s, e):
+        out = [torch.full((B, L), -7, dtype=torch.int32, device="cuda")] + \
+              [torch.full((B, L), -7.0, device="cuda") for _ in range(3)]
+        gpu.fdllm_confidence(logits, mask, s.to(torch.int32).cuda(), e.to(torch.int32).cuda(), *out)
+        torch.cuda.synchronize()
+        return out
+
+    got = run(start, end)
+    pos = torch.arange(L).view(1, L)
+    bad = torch.zeros(B, dtype=torch.bool)
+    bad[[1, 5]] = True
+    want = [torch.full((B, L), v, dtype=t.dtype, device="cuda") for t, v in zip(got, (-1, 0.0, 1.0, 0.0))]
+    for p in range(0, 1024, 32):
+        s, e = torch.minimum(start + p, end), torch.minimum(start + p + 32, end)
+        s[bad], e[bad] = start[bad], end[bad]
+        if not bool((s < e)[~bad].any()):
+            break
+        piece = run(s, e)
+        inside = ((pos >= s.view(B, 1)) & (pos < e.view(B, 1)) & ~bad.view(B, 1)).cuda() & (mask != 0)
+        for w, t in zip(want, piece):
+            w[inside] = t[inside]
+    for name, t, w in zip(("tokens", "conf", "eps", "lse"), got, want):
+        assert torch.equal(t.view(torch.int32), w.view(torch.int32)), name
