@@ -189,18 +189,19 @@ fdllm_status fdllm_reveal(const uint8_t* commit, const int32_t* tokens, int32_t*
  * One whole decoding step (Alg. 1, loop body after the model call):
  * fdllm_confidence, then the selector `sel` with `param` (f, or tau for the
  * threshold rule), then the reveal, fused.  Batches below 256 sequences run as
- * two kernels (rows split over several waves, then the selection); from 768 as
- * one (one workgroup per sequence).  Between, the rows of all sequences are
- * shared evenly by the chip and the selection is a second kernel; that needs
- * the workspace, or tokens, conf and eps all given, and a span of at most
- * about 5600 / B 64-position pieces; otherwise one workgroup per sequence, with
- * the same bits.  When a batch of 768 or more exceeds a multiple of the GPU's
- * compute-unit count by at most 64 sequences, those last sequences run with
- * the small-batch kernels on a stream the library keeps per device, at the
- * same time as the one-kernel part; the call stays asynchronous and can be
- * captured into a HIP graph (the side stream is forked from and joined back to
- * `stream` by events).  That too needs the workspace, or tokens, conf and eps
- * all given; without either, they run in the one kernel.
+ * two kernels (rows split over several waves, then the selection); from 768,
+ * and small ones of 256 or more, as one (one workgroup per sequence).
+ * Otherwise the rows of all sequences are shared evenly by the chip and the
+ * selection is a second kernel; that needs the workspace, or tokens, conf and
+ * eps all given, and a span of at most about 5600 / B 64-position pieces;
+ * otherwise one workgroup per sequence, with the same bits.  When a one-kernel
+ * batch exceeds a multiple of the GPU's compute-unit count by at most 64
+ * sequences, those last sequences run with the small-batch kernels on a stream
+ * the library keeps per device, at the same time as the one-kernel part; the
+ * call stays asynchronous and can be captured into a HIP graph (the side
+ * stream is forked from and joined back to `stream` by events).  That too
+ * needs the workspace, or tokens, conf and eps all given; without either, they
+ * run in the one kernel.
  *   eta, eta_uniform: calibration allowance of FDLLM_SEL_ROBUST (as in
  *   fdllm_select_robust); ignored by the other selectors.
  *   mask [B,L] uint8 (in/out: committed positions are cleared);
@@ -213,8 +214,8 @@ fdllm_status fdllm_reveal(const uint8_t* commit, const int32_t* tokens, int32_t*
  *   smaller workspace (or NULL) is accepted: the results are the same, but a
  *   small batch of blocks of at most 64 positions then streams each row
  *   from one workgroup instead of several.  (The one exception: the last
- *   sequences of a batch of 768 or more, above, run in the one kernel when neither the
- *   workspace nor those three outputs are given; the decisions are the
+ *   sequences of a one-kernel batch, above, run in the one kernel when neither
+ *   the workspace nor those three outputs are given; the decisions are the
  *   oracle's either way, but conf, eps and lse of those sequences are then
  *   not bitwise fdllm_confidence's.)
  */
@@ -238,10 +239,10 @@ fdllm_status fdllm_decode_step(const void* logits, fdllm_dtype dtype, int B, int
  *   FDLLM_ERR_SCRATCH (nothing enqueued).  Small batches need 12 B per
  *   position of the span (when tokens, conf or eps are not given) plus up to
  *   384 B per position of blocks of at most 64 positions; batches of 256 to 767
- *   sequences use 12 B per position where it fits and run without it, with the
- *   same bits, where not; batches of 768
- *   sequences or more need scratch only for the at most 64 sequences beyond a
- *   multiple of the compute-unit count, which run as a small batch.  Those
+ *   sequences that share their rows use 12 B per position where it fits and run without it, with the
+ *   same bits, where not; one-kernel batches need scratch only for the at most
+ *   64 sequences beyond a multiple of the compute-unit count, which run as a
+ *   small batch.  Those
  *   run on `stream` after the one-kernel part instead of beside it on a side
  *   stream (the call creates no stream and no event), with the same bits.
  *   Every call on one GPU uses that GPU's one array: calls that overlap on one

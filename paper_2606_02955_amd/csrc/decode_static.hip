@@ -70,7 +70,7 @@ extern "C" fdllm_status fdllm_decode_step_static(
   if (need > (size_t)FDLLM_STATIC_SCRATCH_BYTES) {
     // a large batch's workspace only holds the outputs the caller does not
     // take; without it the step runs in one kernel, with the same bits
-    if (!fdllm::workspace_optional(B)) return FDLLM_ERR_SCRATCH;
+    if (!fdllm::workspace_optional(B, L, V, dtype)) return FDLLM_ERR_SCRATCH;
     need = 0;
   }
   void* ws = nullptr;

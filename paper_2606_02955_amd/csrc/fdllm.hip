@@ -1584,6 +1584,21 @@ constexpr int kHybridMaxRem = FDLLM_HYBRID_MAX_REM;   // largest remainder run b
 constexpr int kFusedWaves = FDLLM_FUSED_WAVES;   // waves per workgroup in the fused kernel
 constexpr int kTargetWaves = FDLLM_TARGET_WAVES;   // row-streaming waves the split aims for
 
+// Whether the rows of a large batch are shared evenly (make_plan): from
+// kRowsMinBytes of logits in the longest windows on, below which the search
+// and the selection's launch are most of the time (500 blocks of 8 at V = 4000,
+// 32 MB, 17 us in k_fused and 19 to 22 here; 700, 45 MB, 22 to 23 and 22 to
+// 26; 256 of 32, 65 MB, 29 to 30 and 23 to 29), and wherever k_fused would
+// leave the last sequences to a side stream (300 blocks of 8 at V = 4000 60
+// and 21).
+constexpr long long kRowsMinBytes = 40LL << 20;
+static bool rows_plan(int B, int L, int V, fdllm_dtype dt) {
+  if (B < kFusedMinB || B >= kRowsMaxB) return false;
+  const int rem = B % 256;
+  return (rem > 0 && rem <= kHybridMaxRem) ||
+         (double)B * (L < kMaxBlock ? L : kMaxBlock) * V * (dt == FDLLM_BF16 ? 2 : 4) >= (double)kRowsMinBytes;
+}
+
 static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
   Plan p{};
   // slots per sequence the split aims to fill: spans of at most one
@@ -1596,12 +1611,16 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
   // in every kernel that can take it, so the plan can follow from what the
   // caller gives).  Below 768, up to three sequences per CU, they are shared
   // evenly (k_rows): at V = 126464, blocks of 32 with 1..32 masked, 256
-  // sequences 275 -> 198 us, 512 494 -> 364, 700 706 -> 491; 300 sequences,
-  // blocks of 128 with 32..128 masked, V = 32000 338 -> 281; blocks with all
-  // positions masked, where k_fused has no imbalance, lose the selection's
-  // launch: 328 -> 334, 647 -> 653.  At 1024 sequences that launch and the
-  // search cost every full block 17 of 1229 us, so k_fused keeps it.
-  p.rows = p.fused && B < kRowsMaxB;
+  // sequences 275 -> 196 us, 512 494 -> 364; 300 sequences, blocks of 128 with
+  // 32..128 masked, V = 32000 337 -> 268; 512 blocks of 1..64, V = 4000 80 ->
+  // 48.  The host does not know the masks, and where all positions are masked
+  // and the sequences fill the CUs evenly k_fused has no imbalance to lose:
+  // k_rows then pays for its search and the selection's launch, 256 blocks of
+  // 32 at V = 126464 327 -> 331 us, 512 623 -> 623, at V = 32000 181 -> 185, 767
+  // of 16 134 -> 144, 512 of 16 at V = 8000 36 -> 41 (the same with 1..16 masked
+  // 34 -> 30).  At 1024 sequences the launch and the search cost every full
+  // block 17 of 1229 us, so k_fused keeps it.
+  p.rows = rows_plan(B, L, V, dt);
   if (p.fused && !p.rows) {
     // one 8-wave workgroup per sequence fills a CU, so a few sequences beyond
     // a multiple of the CU count would make a second round that leaves most
@@ -2126,7 +2145,7 @@ fdllm_status fdllm_decode_step(const void* logits, fdllm_dtype dtype, int B, int
 
 namespace fdllm {
 
-bool workspace_optional(int B) { return B >= kFusedMinB && B < kRowsMaxB; }
+bool workspace_optional(int B, int L, int V, fdllm_dtype dtype) { return rows_plan(B, L, V, dtype); }
 
 fdllm_status decode_step(const void* logits, fdllm_dtype dtype, int B, int L, int V, uint8_t* mask,
                          const int32_t* block_start, const int32_t* block_end, int32_t* x,

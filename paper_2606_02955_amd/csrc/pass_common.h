@@ -273,9 +273,9 @@ hipError_t launch_select(fdllm_selector sel, const SelectIO& io, int B, int L, f
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Host side: whether a batch of B sequences only uses its workspace for
+// Host side: whether a large batch of these sizes only uses its workspace for
 // outputs that the caller does not take, and does the same without it.
-bool workspace_optional(int B);
+bool workspace_optional(int B, int L, int V, fdllm_dtype dtype);
 
 // Host side, defined with the decode-step kernels: fdllm_decode_step, whose
 // large batches may run their last sequences on a side stream beside the

@@ -280,8 +280,10 @@ def test_workspace_sizes_follow_the_plans(lib):
     # shared rows, by two kernels: tokens, conf and eps pass through memory
     for B, L in [(255, 32), (256, 32), (767, 32), (48, 200), (9, 70)]:
         assert 3 * B * L * 4 <= _ws(lib.fdllm_workspace_size, B, L, 50257, 0) < 3 * (B * L * 4 + 256)
-    # one workgroup per sequence (no workspace) from 768 sequences on
+    # one workgroup per sequence (no workspace) from 768 sequences on, and from
+    # 256 in calls of at most 40 MiB of logits
     assert _ws(lib.fdllm_workspace_size, 768, 32, V, 0) == 0
+    assert _ws(lib.fdllm_workspace_size, 256, 16, 5119, 0) == 0 < _ws(lib.fdllm_workspace_size, 256, 16, 5120, 0)
     # LM head: the candidates' list, the partial results (24 bytes for each of
     # at most 256 vocabulary ranges a position) and the outputs, no logits
     for B, L, d in [(1, 32, 4096), (2, 32, 4096), (2, 32, 4032), (1, 65, 4096), (8, 32, 4096)]:

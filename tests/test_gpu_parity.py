@@ -495,7 +495,11 @@ def test_very_confident_rows_eps(gpu, B, L, V, dt):
                                               (300, 65, 512, torch.float32, 65), (511, 130, 64, torch.bfloat16, 130),
                                               (767, 8, 1001, torch.bfloat16, 8), (768, 8, 1001, torch.bfloat16, 8),
                                               (400, 300, 33, torch.float32, 300), (256, 1024, 16, torch.bfloat16, 1024),
-                                              (260, 33, 126464, torch.bfloat16, 33)])
+                                              (260, 33, 126464, torch.bfloat16, 33),
+                                              # at least 40 MiB of logits, or a few beyond 256: the rows are shared
+                                              (256, 64, 1300, torch.bfloat16, 64), (511, 130, 400, torch.bfloat16, 130),
+                                              (400, 300, 200, torch.float32, 300), (256, 1024, 100, torch.bfloat16, 1024),
+                                              (767, 8, 5000, torch.bfloat16, 8), (257, 1, 512, torch.bfloat16, 1)])
 @pytest.mark.parametrize("p_mask", [0.0, 0.1, 1.0])
 def test_shared_rows_equal_fused_bits(gpu, B, L, V, dt, window, p_mask):
     """Evenly shared rows (outputs given) and one workgroup per sequence (no
@@ -509,6 +513,8 @@ def test_shared_rows_equal_fused_bits(gpu, B, L, V, dt, window, p_mask):
     start[4], end[4] = 0, L + 1                    # invalid
     inp.start, inp.end = start, end
     say(f"[shared rows] {inp.name} p_mask={p_mask}")
+    shared = B < 768 and (0 < B % 256 <= 64 or inp.logits.numel() * inp.logits.element_size() >= 40 << 20)
+    assert (gpu.fdllm_workspace_size(B, L, V, dt) > 0) == shared        # place for tokens, conf, eps
     ref = gpu_confidence(gpu, inp)
     got = []
     for outs in (True, False):
