@@ -286,3 +286,11 @@ if __name__ == "__main__":
     import sys
     with open(sys.argv[1]) as fh:
         print(render_report([json.loads(line) for line in fh if line.strip()]), end="")
+
+
+def remainder_batch(spec):
+    """(B, r) of a batch "kn+r": r sequences beyond k times the CU count n."""
+    k, r = spec.split("n+")
+    n = torch.cuda.get_device_properties(0).multi_processor_count
+    B = int(k) * n + int(r)
+    return B, B % n

@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads
 from parity import (say, row_source, candidates, compare_rows, gpu_confidence,
-                    oracle_confidence_subset, check_defaults, compare_selection, sub_mask)
+                    oracle_confidence_subset, check_defaults, compare_selection, sub_mask, remainder_batch)
 
 pytestmark = pytest.mark.gpu
 
@@ -373,19 +373,32 @@ def test_decode_step_row_parts_match_single_workgroup(gpu, B, L, V, dt, window):
         assert torch.equal(o1[k].view(torch.uint8), o2[k].view(torch.uint8)), k
 
 
+# beyond one CU multiple the rows are shared; beyond three on a 256-CU part, up
+# to 64 sequences more take the small-batch plan, on a side stream
 @pytest.mark.parametrize("B,L,V,dt,window", [(260, 32, 126464, torch.bfloat16, 32),
                                               (300, 12, 20000, torch.float32, 12),
                                               (257, 70, 3000, torch.bfloat16, 70),
-                                              # the remainder's limits on a 256-CU part: 64 beyond
-                                              # one and two CU multiples, then 65 (all fused)
                                               (320, 8, 4096, torch.bfloat16, 8),
                                               (576, 8, 2048, torch.float32, 8),
-                                              (321, 8, 4096, torch.float32, 8)])
+                                              (321, 8, 4096, torch.float32, 8),
+                                              ("3n+1", 8, 4096, torch.bfloat16, 8),
+                                              ("3n+1", 33, 30000, torch.bfloat16, 33),
+                                              ("3n+64", 8, 4096, torch.bfloat16, 8),
+                                              ("3n+65", 8, 4096, torch.float32, 8),     # all in one kernel
+                                              ("3n+9", 70, 3000, torch.bfloat16, 70),
+                                              ("4n+6", 12, 20000, torch.float32, 12),
+                                              ("4n+40", 100, 1001, torch.bfloat16, 100)])
 def test_fused_step_remainder_bits(gpu, B, L, V, dt, window):
-    """Sequences beyond a multiple of the CU count take the small-batch plan
-    beside the fused kernel: the decode step gives fdllm_confidence's bits for
-    every row, the same with and without a workspace, and the oracle's
-    results (checked on the remainder and a few fused sequences)."""
+    """Sequences beyond a multiple of the CU count: the decode step gives
+    fdllm_confidence's bits for every row, the same with and without a
+    workspace, and the oracle's results (checked on the last and a few other
+    sequences).  Those beyond three or more CU multiples take the small-batch
+    plan beside the fused kernel, and the workspace holds their outputs."""
+    if isinstance(B, str):
+        B, rem = remainder_batch(B)
+        need = gpu.fdllm_workspace_size(B, L, V, dt)
+        assert 12 * rem * L <= need if 0 < rem <= 64 else need == 0
+        assert need < 12 * B * L
     inp = _case(B, L, V, dt, window, seed=B + L)
     say(f"[fused step remainder] {inp.name}")
     ref = gpu_confidence(gpu, inp)

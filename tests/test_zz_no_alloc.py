@@ -9,7 +9,7 @@ import torch
 
 import paper_2606_02955_amd as fd
 import workloads
-from parity import say
+from parity import remainder_batch, say
 
 pytestmark = pytest.mark.gpu
 
@@ -65,15 +65,18 @@ def _same(a, b):
 # workgroups with their parts in scratch; rows split within a workgroup; wide
 # spans), large batches (one workgroup per sequence, their last sequences
 # beyond a multiple of the CU count as a small batch: on a side stream for
-# fdllm_decode_step, after the one-kernel part for the static call), and
-# calls without tokens / conf / eps, whose values then live in the scratch
+# fdllm_decode_step, after the one-kernel part for the static call; or their
+# rows shared by the chip), and calls without tokens / conf / eps, whose values then live in the scratch
 CASES = [
     (8, 32, 126464, torch.bfloat16, "profile", 1.0, True),
     (2, 16, 126464, torch.bfloat16, "factor", 1.0, False),
     (40, 64, 50000, torch.bfloat16, "threshold", 0.9, True),
     (3, 32, 5000, torch.float32, "robust", 0.9, False),
+    ("3n+44", 8, 4096, torch.float32, "threshold", 0.9, False),
+    ("3n+4", 8, 4096, torch.bfloat16, "profile", 0.75, True),
     (300, 8, 4096, torch.float32, "threshold", 0.9, False),
     (260, 8, 4096, torch.bfloat16, "profile", 0.75, True),
+    (400, 64, 2000, torch.bfloat16, "profile", 1.0, False),
     (24, 200, 8000, torch.bfloat16, "profile", 1.0, False),
     (1, 32, 126464, torch.float32, "profile", 1.0, False),
 ]
@@ -82,6 +85,10 @@ CASES = [
 def test_static_matches_workspace_calls_in_a_row(gpu):
     lib = fd.load()
     for k, (B, L, V, dt, rule, param, scores) in enumerate(CASES):
+        if isinstance(B, str):
+            B, rem = remainder_batch(B)
+            need = fd.fdllm_workspace_size(B, L, V, dt)
+            assert 12 * rem * L <= need < 12 * B * L       # the last sequences are a small batch
         say(f"[static scratch] call {k}: B={B} L={L} V={V} {dt} {rule}({param}) scores={scores}")
         inp = workloads.random_case(B, L, V, dt, device="cuda", seed=70 + k,
                                     window=min(L, 160))
