@@ -104,8 +104,6 @@ k_synth(uint16_t* __restrict__ logits, int B, int L, int V, int blk,
   const float six_u2 = __fmul_rn(6.0f, u2);
   const float h = u1 < 0.6f ? __fadd_rn(8.0f, six_u2) : six_u2;
   uint16_t* row = logits + ((size_t)b * L + i) * (size_t)V;
-  // a row starts on a 2-byte boundary; 16-byte stores where it allows them
-  const bool wide = ((uintptr_t)row & 15u) == 0;
 #pragma unroll 1
   for (int trip = 0; trip < kSynthTrips; ++trip) {
     const uint32_t v0 = blockIdx.y * kSynthRun + (uint32_t)(trip * kSynthThreads + (int)threadIdx.x) * 8u;
@@ -122,8 +120,10 @@ k_synth(uint16_t* __restrict__ logits, int B, int L, int V, int blk,
       if (v0 + 2u * j + 1u == tok) hi = __fadd_rn(hi, h);
       out[j] = bf16_rne(lo) | (bf16_rne(hi) << 16);
     }
-    if (wide && v0 + 8u <= (uint32_t)V) {
-      *reinterpret_cast<uint4*>(row + v0) = make_uint4(out[0], out[1], out[2], out[3]);
+    if (v0 + 8u <= (uint32_t)V) {
+      // rows start on any 2-byte boundary, and so may a 16-byte store (a store
+      // an entry, where V is no multiple of 8: V = 126460 44 us, not 21)
+      __builtin_memcpy(row + v0, out, 16);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
