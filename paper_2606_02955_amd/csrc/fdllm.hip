@@ -698,33 +698,35 @@ __device__ __forceinline__ void rows_split(const typename Vec::Mem* __restrict__
 // only B W row groups are launched, however long the span L.
 //
 // A row group is launched whether or not its positions are masked: the best
-// grid for windows of at most W, whatever the span.  The positions beyond W of
-// a longer window would take second turns in some row groups.  So with kLong
-// (spans that can hold one: at most kLongMaxB sequences, W = 32, B L < 2^31)
-// the row groups of longer windows share the candidate rows of all such
+// grid for windows of at most W, whatever the span, and for whole multiples of
+// W, whose row groups have the same turns.  The positions beyond a multiple
+// would take one turn more in some row groups.  So with kUneven (spans that
+// can hold such a window: at most kUnevenMaxB sequences, W = 32, B L < 2^31)
+// the row groups of uneven windows share the candidate rows of all such
 // windows evenly, by number (rows_split), with the same bits; the first
 // `groups` of their workgroups, as many as the chip holds, do the work.  The
-// windows decide, not the span, and a workgroup of a short window looks at no
+// windows decide, not the span, and a workgroup of another window looks at no
 // other sequence's: reading all bounds first costs every workgroup a round
 // trip (64 blocks of 1..32 in spans of 512 66.7 -> 68.3 us).  At V = 126464
 // 100 full blocks of 48 227 -> 203 us, 24 in spans of 96 86 -> 72, 16 of 100
 // in spans of 800 118 -> 104; 48 blocks of 5..40 in spans of 200 at V = 50257
 // 62 -> 39, 100 of 5..40 in spans of 320 at V = 32000 59 -> 41.  Blocks of 32
 // are best in their row groups: sharing their rows took 64 full blocks in
-// spans of 293 from 95 to 107 us, 200 in spans of 100 at V = 32000 84 to 98.
-constexpr int kLongMaxB = 255;
-constexpr int kLongChunks = 1024;       // LDS room; more chunks: row groups
+// spans of 293 from 95 to 107 us, 200 in spans of 100 at V = 32000 84 to 98;
+// so are multiples: 167 full blocks of 128 at V = 39384 299 against 331.
+constexpr int kUnevenMaxB = 255;
+constexpr int kUnevenChunks = 1024;     // LDS room; more chunks: row groups
 
-// The sequences with windows longer than W, by a workgroup of NW waves.
-struct LongSeqs {
-  static constexpr int kWords = (kLongMaxB + kWave - 1) / kWave;
+// The sequences with uneven windows.
+struct UnevenSeqs {
+  static constexpr int kWords = (kUnevenMaxB + kWave - 1) / kWave;
   unsigned long long word[kWords];     // a bit a sequence
   int longest[kWords];
   unsigned char seq[kWords * kWave];   // their numbers and windows
   RowsWindow win[kWords * kWave];
 };
 
-template <class Vec, int U, int S, bool kLong>
+template <class Vec, int U, int S, bool kUneven>
 __global__ void __launch_bounds__(SplitShape<S>::kThreads)
 k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nvec,
              const uint8_t* __restrict__ mask, const int32_t* __restrict__ bstart,
@@ -753,58 +755,59 @@ k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nve
     }
   }
   const size_t row0 = (size_t)b * L;
-  if constexpr (kLong) {
-    if (len > W) {                      // the workgroup's row groups are of one sequence
-      __shared__ RowsChunk s_chunk[kLongChunks];
+  if constexpr (kUneven) {
+    if (len > W && len % 32 != 0) {     // the workgroup's row groups are of one sequence
+      __shared__ RowsChunk s_chunk[kUnevenChunks];
       __shared__ RowsRing<Shape::kWaves, S> s_ring;
-      __shared__ LongSeqs s_long;
-      static_assert(Shape::kWaves >= LongSeqs::kWords, "a wave a word");
+      __shared__ UnevenSeqs s_uneven;
+      static_assert(Shape::kWaves >= UnevenSeqs::kWords, "a wave a word");
       const int at = wave * kWave + lane;
-      bool is_long = false;
+      bool is_uneven = false;
       int n = 0, s1 = 0;
-      if (wave < LongSeqs::kWords) {
+      if (wave < UnevenSeqs::kWords) {
         if (at < B) {
           s1 = bstart[at];
           const int e1 = bend[at];
           if (window_ok(s1, e1, L)) n = e1 - s1;
         }
-        is_long = n > W;
-        const unsigned long long word = __ballot(is_long);
-        const int longest = -wave_min(-n);
+        is_uneven = n > W && n % 32 != 0;
+        const unsigned long long word = __ballot(is_uneven);
+        const int longest = -wave_min(is_uneven ? -n : 0);
         if (lane == 0) {
-          s_long.word[wave] = word;
-          s_long.longest[wave] = longest;
+          s_uneven.word[wave] = word;
+          s_uneven.longest[wave] = longest;
         }
       }
       __syncthreads();
-      int n_long = 0, longest = 0, own = 0, mine = 0;   // before sequence b, before sequence `at`
+      int n_uneven = 0, longest = 0, own = 0, mine = 0;   // before sequence b, before sequence `at`
   #pragma unroll
-      for (int i = 0; i < LongSeqs::kWords; ++i) {
-        const unsigned long long word = s_long.word[i];
+      for (int i = 0; i < UnevenSeqs::kWords; ++i) {
+        const unsigned long long word = s_uneven.word[i];
         auto below = [&](int seq) {
           const int bits = seq - i * kWave;
           return __popcll(bits <= 0 ? 0ull : bits >= kWave ? word : word & ((1ull << bits) - 1ull));
         };
         own += below(b);
         mine += below(at);
-        n_long += __popcll(word);
-        longest = max(longest, s_long.longest[i]);
+        n_uneven += __popcll(word);
+        longest = max(longest, s_uneven.longest[i]);
       }
       const int C = (longest + kWave - 1) / kWave;
-      if (n_long * C <= kLongChunks) {
+      if (n_uneven * C <= kUnevenChunks) {
         constexpr int kPer = 32 / Shape::kRows;  // workgroups a sequence
         const int group = own * kPer + (int)(blockIdx.x % kPer);
-        const int n_groups = min(groups, n_long * kPer);
+        const int n_groups = min(groups, n_uneven * kPer);
         if (group >= n_groups) return;
-        if (is_long) {
-          s_long.seq[mine] = (unsigned char)at;
-          s_long.win[mine] = RowsWindow{at * L + s1, n};
+        if (is_uneven) {
+          s_uneven.seq[mine] = (unsigned char)at;
+          s_uneven.win[mine] = RowsWindow{at * L + s1, n};
         }
         __syncthreads();
         rows_split<Vec, U, S, Shape::kWaves>(
-            logits, __builtin_amdgcn_readfirstlane(n_long), [&](int j) { return (int)s_long.seq[j]; },
-            [&](int j) { return s_long.win[j]; }, L, __builtin_amdgcn_readfirstlane(C), nvec, mask, B * L, out, __builtin_amdgcn_readfirstlane(group),
-            __builtin_amdgcn_readfirstlane(n_groups), s_chunk, s_ring, s_kept);
+            logits, __builtin_amdgcn_readfirstlane(n_uneven), [&](int j) { return (int)s_uneven.seq[j]; },
+            [&](int j) { return s_uneven.win[j]; }, L, __builtin_amdgcn_readfirstlane(C), nvec, mask, B * L, out,
+            __builtin_amdgcn_readfirstlane(group), __builtin_amdgcn_readfirstlane(n_groups), s_chunk, s_ring,
+            s_kept);
         return;
       }
     }
@@ -1554,7 +1557,7 @@ struct Plan {
   bool fused;   // one workgroup per sequence, selection in the same kernel
   bool rows;    // fused, where they fit and the outputs have a place: evenly shared rows,
                 // then the selection
-  bool lengths; // not fused: evenly shared rows where a window is longer than the row
+  bool uneven;  // not fused: evenly shared rows where a window is no multiple of the row
                 // groups (decided on the device)
   int split;    // wavefronts per row in the confidence kernel
   int parts;    // decode step with a workspace: split over split / 4 workgroups (0: no)
@@ -1643,10 +1646,10 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
     // a row split 8 or 16 ways fills one CU; blocks of at most one wavefront
     // can take their rows' parts from several workgroups instead
     if (L <= kWaveBlock && p.split >= 8) p.parts = p.split;
-    // spans that can hold a window longer than the row groups: see
+    // spans that can hold a window of more row groups than there are: see
     // k_confidence.  Parts from several workgroups are better than either
     // (40 full blocks of 40 82 against 97 us).
-    p.lengths = B >= kGroups32MinB && B <= kLongMaxB && L > row_groups(B, L) && !p.parts &&
+    p.uneven = B >= kGroups32MinB && B <= kUnevenMaxB && L > row_groups(B, L) && !p.parts &&
                 (long long)B * L <= 0x7fffffffLL;
   }
   return p;
@@ -1660,9 +1663,9 @@ static bool vec_path(const void* logits, int V, fdllm_dtype dt) {
 template <class Vec>
 static hipError_t launch_confidence_t(const void* logits, int B, int L, int nvec, int split,
                                       const uint8_t* mask, const int32_t* bs, const int32_t* be,
-                                      RowOut out, bool lengths, hipStream_t st) {
+                                      RowOut out, bool uneven, hipStream_t st) {
   const long long nvslots = (long long)B * row_groups(B, L);   // window-relative
-  const int cus = lengths ? device_cus() : 0;
+  const int cus = uneven ? device_cus() : 0;
   const auto* lg = (const typename Vec::Mem*)logits;
 #define FDLLM_CONF_CASE(SPLIT)                                                                  \
   case SPLIT: {                                                                                 \
@@ -1728,15 +1731,15 @@ static hipError_t launch_confidence_parts(const void* logits, fdllm_dtype dt, in
 
 static hipError_t launch_confidence(const void* logits, fdllm_dtype dt, int B, int L, int V,
                                     int split, const uint8_t* mask, const int32_t* bs,
-                                    const int32_t* be, RowOut out, bool lengths, hipStream_t st) {
+                                    const int32_t* be, RowOut out, bool uneven, hipStream_t st) {
   if (vec_path(logits, V, dt)) {
     if (dt == FDLLM_BF16)
-      return launch_confidence_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, lengths, st);
-    return launch_confidence_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, lengths, st);
+      return launch_confidence_t<VecBf16x8>(logits, B, L, V / 8, split, mask, bs, be, out, uneven, st);
+    return launch_confidence_t<VecF32x4>(logits, B, L, V / 4, split, mask, bs, be, out, uneven, st);
   }
   if (dt == FDLLM_BF16)
-    return launch_confidence_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, lengths, st);
-  return launch_confidence_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, lengths, st);
+    return launch_confidence_t<VecBf16Any>(logits, B, L, V, split, mask, bs, be, out, uneven, st);
+  return launch_confidence_t<VecF32Any>(logits, B, L, V, split, mask, bs, be, out, uneven, st);
 }
 
 template <int R, bool Robust>
@@ -1964,7 +1967,7 @@ static fdllm_status step_split(const Plan& p, fdllm_selector sel, const void* lo
     err = launch_select(sel, io, B, L, param, st, p.parts, parts, out);
     return err == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
   }
-  err = launch_confidence(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, p.lengths, st);
+  err = launch_confidence(logits, dtype, B, L, V, p.split, mask, block_start, block_end, out, p.uneven, st);
   if (err != hipSuccess) return FDLLM_ERR_HIP;
   err = launch_select(sel, io, B, L, param, st);
   return err == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
@@ -2059,7 +2062,7 @@ fdllm_status fdllm_confidence(const void* logits, fdllm_dtype dtype, int B, int 
   // step splits them, so that both give the same bits
   const int b0 = B - p.rem;
   hipError_t err = launch_confidence(logits, dtype, b0, L, V, p.split, mask, block_start, block_end,
-                                     out, p.lengths, st);
+                                     out, p.uneven, st);
   if (err == hipSuccess && p.rem) {
     const size_t r0 = (size_t)b0 * (size_t)L;
     const size_t esize = dtype == FDLLM_BF16 ? 2 : 4;
