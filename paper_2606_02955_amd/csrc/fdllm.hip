@@ -1555,8 +1555,8 @@ __global__ void __launch_bounds__(256) k_check(const typename Vec::Mem* __restri
 // ---------------------------------------------------------------------------
 struct Plan {
   bool fused;   // one workgroup per sequence, selection in the same kernel
-  bool rows;    // fused, where they fit and the outputs have a place: evenly shared rows,
-                // then the selection
+  bool rows;    // where they fit (and, fused, where the outputs have a place): evenly
+                // shared whole rows (k_rows), then the selection
   bool uneven;  // not fused: evenly shared rows where a window is no multiple of the row
                 // groups (decided on the device)
   int split;    // wavefronts per row in the confidence kernel
@@ -1650,7 +1650,16 @@ static Plan make_plan(int B, int L, int V, fdllm_dtype dt) {
     // k_confidence.  Parts from several workgroups are better than either
     // (40 full blocks of 40 82 against 97 us).
     p.uneven = B >= kGroups32MinB && B <= kUnevenMaxB && L > row_groups(B, L) && !p.parts &&
-                (long long)B * L <= 0x7fffffffLL;
+               (long long)B * L <= 0x7fffffffLL;
+    // Whole rows of spans that are no multiple of 32, if few chunks can hold
+    // candidates: k_rows, the same with one list a CU, whatever the windows.
+    // 250 blocks of 50..100 at V = 8000 86 -> 77 us, 60 at V = 4000 34 -> 30; blocks
+    // of 32 do not lose there (200 in spans of 100 at V = 8000 35.2 and 35.4, with
+    // 1..32 masked 28.9 -> 26.5; 250 in spans of 200 40.0 and 40.4).  A multiple
+    // of 32 most likely holds those, which then lose a little (100 in spans of
+    // 512 26.0 -> 27.3), and long spans lose more (250 in spans of 1024 at
+    // V = 4000 35 -> 40).
+    p.rows = p.uneven && p.split == 1 && L % 32 != 0 && B * rows_chunks(L) <= kUnevenChunks;
   }
   return p;
 }
@@ -1956,6 +1965,11 @@ static fdllm_status step_split(const Plan& p, fdllm_selector sel, const void* lo
   const RowOut out{tokens, conf, eps, lse};
   SelectIO io{conf, eps, mask, block_start, block_end, commit, n_commit, tokens, x, etain};
   hipError_t err;
+  if (p.rows && rows_ok(logits, dtype, B, L, V)) {
+    err = launch_rows(logits, dtype, B, L, V, mask, block_start, block_end, out, st);
+    if (err != hipSuccess) return FDLLM_ERR_HIP;
+    return launch_select(sel, io, B, L, param, st) == hipSuccess ? FDLLM_OK : FDLLM_ERR_HIP;
+  }
   if (p.parts && workspace && workspace_bytes >= out_bytes_for(B, L) +
                                                      align256(n * p.parts * sizeof(WavePartial))) {
     // the rows' parts from several workgroups each, combined by the selection

@@ -663,7 +663,8 @@ def test_shared_rows_longest_span(gpu):
     (12, 1024, 20000, torch.float32),          # windows of up to 16 chunks
     (128, 96, 70000, torch.bfloat16),          # 4 ways
     (200, 64, 40000, torch.float32),           # 2 ways
-    (255, 65, 3000, torch.bfloat16),           # whole rows, as many sequences as take this path
+    (255, 96, 3000, torch.bfloat16),           # whole rows, as many sequences as take this path
+    (255, 65, 3000, torch.float32),            # whole rows of all windows, one list a CU
     (64, 1024, 300, torch.bfloat16),           # as many chunks as fit, or more
     (200, 1024, 64, torch.float32),            # more: row groups
     (300, 130, 200, torch.bfloat16),           # a large batch: the rows of all sequences
