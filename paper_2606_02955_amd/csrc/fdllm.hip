@@ -780,7 +780,7 @@ k_confidence(const typename Vec::Mem* __restrict__ logits, int B, int L, int nve
       }
       __syncthreads();
       int n_uneven = 0, longest = 0, own = 0, mine = 0;   // before sequence b, before sequence `at`
-  #pragma unroll
+#pragma unroll
       for (int i = 0; i < UnevenSeqs::kWords; ++i) {
         const unsigned long long word = s_uneven.word[i];
         auto below = [&](int seq) {
